@@ -99,11 +99,10 @@ __device__ __forceinline__ void collide_vjp(const R (&g)[9], const R (&mu)[9], c
         ir = n.ir;
         ux = n.ux;
         uy = n.uy;
-        const R jx = n.jx, jy = n.jy, uxx = n.uxx, uyy = n.uyy, u2 = n.u2;
+        const R jx = n.jx, jy = n.jy, uxx = n.uxx, uyy = uy * uy, u2 = n.u2;
         const R dN = n.dN, dP = n.dP, tT = n.tT;
-        const R(&ds)[9] = n.ds;
-        const R(&dh)[9] = n.dh;
-        const R(&w)[9] = n.w;
+        R ds[9], dh[9], w[9];
+        unscaled(n, ds, dh, w);
         const R ratio = n.ratio, bsum = n.b;
         const bool active = n.active;
         R gam = n.gam;

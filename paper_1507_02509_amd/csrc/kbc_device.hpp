@@ -230,24 +230,49 @@ __device__ __forceinline__ R exact_gamma(R gam, const R (&ds)[9], const R (&dh)[
 // Forward quantities of one KBC collision at a node, shared by the step
 // (collide) and its adjoint (collide_vjp) so that both take the same
 // decisions on the same values.
+//
+// ds, dh and w are kept in scaled units: the rest population's parts at half
+// their value and the diagonals' at twice (node_scale), their weights at four
+// times and a quarter (1 / node_scale^2), so that ds_i dh_i w_i is unchanged.  In
+// these units the populations of ds and dh are plain sums of the moments (no
+// multiplications by 1/4, 1/2, 2, 4), the nine denominators of the weights
+// share their leading terms, and the rest population's denominator is one of
+// those terms.
 template <typename R> struct KbcNode {
     R dr, rho, ir, jx, jy;              // rho - rho0, rho, 1 / rho, rho u
-    R ux, uy, uxx, uyy, u2;
+    R ux, uy, uxx, u2;
     R dT, dN, dP;                       // non-equilibrium T, N, Pi
     R tT;                               // T of the shear part: dT (A, C) or 0 (B, D)
-    R ds[9], dh[9];                     // shear and higher-order parts of f - feq
-    R w[9];                             // rho / feq_i (entropic weights)
+    R ds[9], dh[9];                     // shear and higher-order parts of f - feq (scaled)
+    R w[9];                             // rho / feq_i (entropic weights, scaled)
     R ratio, b;                         // <ds|dh> / <dh|dh> and <dh|dh>
     R gam;                              // stabiliser used (estimate, 2 when guarded, or fixed)
     bool active;                        // gamma follows eq. (result21) (not guarded, not fixed)
 };
+template <typename R> constexpr R node_scale(int i) { return i == 0 ? R(0.5) : (i < 5 ? R(1) : R(2)); }
+
+// <ds|ds> of the guard is compared only where <dh|dh> is small: with
+// |u|^2 < 1/6 every 1 + e_i is at least 1/4 (3 c.u + 4.5 (c.u)^2 >= -1/2), so
+// 1 / (W_i (1 + e_i)) <= 4 / W_i, and with the bounds of |ds_i| in the moments
+// (|Q| <= 0.82 |Pi| + 0.21 (|T| + |N|), |A| <= 0.34 |Pi| + 0.084 (|T| + |N|))
+// <ds|ds> <= 1110 Pi^2 + 128 T^2 + 98 N^2; the constant leaves room for rounding.
+template <typename R> constexpr R guard_bound() { return R(1300); }
 
 // Written for instruction count: the kernels that call it issue one vector
 // instruction per operation here and are bound by that issue rate, so every
 // product-plus-sum is an explicit FMA (contraction is off) and scale factors
 // are folded into the moments before they are spread back to populations.
+// FP32 KBC-B takes 151 vector instructions per collision (181 with unscaled
+// populations spread one by one and <ds|ds> always formed).  The fused step of
+// an FP16 lattice, bound by instruction issue, went from 35.1 to 31.8 us per
+// pair of steps at 1921 x 1083, of FP64 2-3 %; FP32 at 8192^2 from 975 to 918,
+// where it now moves 5.3 TB/s and is bound by memory as much.
+// The natural-moment variants (C, D) sum in the order that has been checked
+// over 2000-step gradients: there too every scale is a power of two.
 template <typename R, int VAR, int GM>
 __device__ __forceinline__ void kbc_forward(const R (&g)[9], const Coef<R>& K, KbcNode<R>& n) {
+    constexpr bool kCentral = (VAR == VA || VAR == VB);   // s in the co-moving frame, eq. (cm)
+    constexpr bool kTrace = (VAR == VA || VAR == VC);     // T belongs to s
     // conserved moments, eq. (moments) restricted to the deviations
     const R s13 = g[1] + g[3], s24 = g[2] + g[4], s57 = g[5] + g[7], s68 = g[6] + g[8];
     const R d13 = g[1] - g[3], d24 = g[2] - g[4], d57 = g[5] - g[7], d68 = g[6] - g[8];
@@ -259,13 +284,11 @@ __device__ __forceinline__ void kbc_forward(const R (&g)[9], const Coef<R>& K, K
     const R rho = K.rho0 + dr;
     const R ir = rcpR(rho);
     const R ux = jx * ir, uy = jy * ir;
-    const R uxx = ux * ux, uyy = uy * uy, u2 = uxx + uyy;
-    const R upv = ux + uy, umv = ux - uy;
+    const R uxx = ux * ux, uyy = uy * uy;
+    const R u2 = kCentral ? fmaR(uy, uy, uxx) : uxx + uyy;
     n.dr = dr; n.rho = rho; n.ir = ir; n.jx = jx; n.jy = jy;
-    n.ux = ux; n.uy = uy; n.uxx = uxx; n.uyy = uyy; n.u2 = u2;
+    n.ux = ux; n.uy = uy; n.uxx = uxx; n.u2 = u2;
 
-    constexpr bool kCentral = (VAR == VA || VAR == VB);   // s in the co-moving frame, eq. (cm)
-    constexpr bool kTrace = (VAR == VA || VAR == VC);     // T belongs to s
     // non-equilibrium moments of df = f - feq (feq of second order, c_s^2 = 1/3)
     const R juy = jy * uy;
     const R jsum = fmaR(jx, ux, juy);          // rho |u|^2
@@ -276,88 +299,69 @@ __device__ __forceinline__ void kbc_forward(const R (&g)[9], const Coef<R>& K, K
     const R dQx = fmaR(R(-1.0 / 3.0), jx, mq);
     const R dQy = fmaR(R(-1.0 / 3.0), jy, pq);
     const R dA = fmaR(R(-1.0 / 3.0), jsum, fmaR(R(-1.0 / 9.0), dr, sd));
-    const R uxy = ux * uy;
     n.dT = dT; n.dN = dN; n.dP = dP;
     n.tT = kTrace ? dT : R(0);
 
-    // Shear part s, Table kbc_moment_grouping: (T_s, N, Pi, Q_xyy,s, Q_yxx,s,
-    // A_s), all scaled by 1/4 (tq, nq, pq4, xq, yq, aq).  Central variants
-    // take the linear part of eq. (cm) at the node's velocity.
-    const R nq = R(0.25) * dN, pq4 = R(0.25) * dP;
-    R xq = R(0), yq = R(0), aq = R(0);
-    if constexpr (kCentral) {
-        const R p2 = R(0.5) * dP, n8 = R(0.125) * dN;
-        if constexpr (kTrace) {
-            const R t8 = R(0.125) * dT;
-            xq = fmaR(uy, p2, ux * (t8 - n8));
-            yq = fmaR(ux, p2, uy * (t8 + n8));
-            aq = fmaR(uxy, dP, fmaR(u2, t8, -((uxx - uyy) * n8)));
-        } else {
-            xq = fmaR(uy, p2, -(ux * n8));
-            yq = fmaR(ux, p2, uy * n8);
-            aq = fmaR(uxy, dP, -((uxx - uyy) * n8));
-        }
-    }
-    // populations of s, eq. (momentsD2Q9) without mass and momentum
+    // Shear part s, Table kbc_moment_grouping, from (T_s +- N) / 4, Q_xyy,s / 2
+    // (ox), Q_yxx,s / 2 (oy) and A_s / 2 (a2).  Central variants take the
+    // linear part of eq. (cm) at the node's velocity, in which
+    // A_s = u_x Q_xyy,s + u_y Q_yxx,s.
+    const R n4 = R(0.25) * dN;
+    const R tq = R(0.25) * dT;
+    const R tpn = kTrace ? tq + n4 : n4, tmn = kTrace ? tq - n4 : -n4;
+    const R p2 = R(0.5) * dP;
     R (&ds)[9] = n.ds;
-    {
-        R tpn, tmn;                              // (T_s +- N) / 4
-        if constexpr (kTrace) {
-            const R tq = R(0.25) * dT;
-            tpn = tq + nq;
-            tmn = tq - nq;
-        } else {
-            tpn = nq;
-            tmn = -nq;
-        }
-        if constexpr (kCentral) {
-            ds[0] = kTrace ? fmaR(R(4), aq, -dT) : R(4) * aq;
-            ds[1] = fmaR(R(-2), xq + aq, tpn);
-            ds[3] = fmaR(R(2), xq - aq, tpn);
-            ds[2] = fmaR(R(-2), yq + aq, tmn);
-            ds[4] = fmaR(R(2), yq - aq, tmn);
-            const R ap = aq + pq4, am = aq - pq4, xp = xq + yq, xm = xq - yq;
-            ds[5] = ap + xp;
-            ds[7] = ap - xp;
-            ds[6] = am - xm;
-            ds[8] = am + xm;
-        } else {
-            ds[0] = kTrace ? -dT : R(0);
-            ds[1] = tpn;
-            ds[3] = tpn;
-            ds[2] = tmn;
-            ds[4] = tmn;
-            ds[5] = pq4;
-            ds[7] = pq4;
-            ds[6] = -pq4;
-            ds[8] = -pq4;
-        }
+    R ox = R(0), oy = R(0), a2 = R(0);
+    if constexpr (kCentral) {
+        ox = fmaR(uy, dP, ux * tmn);
+        oy = fmaR(ux, dP, uy * tpn);
+        a2 = fmaR(ux, ox, uy * oy);
+        const R e1 = tpn - a2, e2 = tmn - a2;
+        ds[0] = kTrace ? fmaR(R(-0.5), dT, a2) : a2;
+        ds[1] = e1 - ox;
+        ds[3] = e1 + ox;
+        ds[2] = e2 - oy;
+        ds[4] = e2 + oy;
+        const R ap = a2 + p2, am = a2 - p2, xp = ox + oy, xm = ox - oy;
+        ds[5] = ap + xp;
+        ds[7] = ap - xp;
+        ds[6] = am - xm;
+        ds[8] = am + xm;
+    } else {
+        ds[0] = kTrace ? R(-0.5) * dT : R(0);
+        ds[1] = tpn;
+        ds[3] = tpn;
+        ds[2] = tmn;
+        ds[4] = tmn;
+        ds[5] = p2;
+        ds[7] = p2;
+        ds[6] = -p2;
+        ds[8] = -p2;
     }
-    // higher-order part h = df - s: moments (T - T_s, 0, 0, dQ - Q_s, dA - A_s) / 4
+    // higher-order part h = df - s: moments (T - T_s, 0, 0, dQ - Q_s, dA - A_s)
     R (&dh)[9] = n.dh;
     {
-        const R xh = kCentral ? fmaR(R(0.25), dQx, -xq) : R(0.25) * dQx;
-        const R yh = kCentral ? fmaR(R(0.25), dQy, -yq) : R(0.25) * dQy;
-        const R ah = kCentral ? fmaR(R(0.25), dA, -aq) : R(0.25) * dA;
+        const R xh = kCentral ? fmaR(R(0.5), dQx, -ox) : R(0.5) * dQx;
+        const R yh = kCentral ? fmaR(R(0.5), dQy, -oy) : R(0.5) * dQy;
+        const R ah = kCentral ? fmaR(R(0.5), dA, -a2) : R(0.5) * dA;
+        dh[0] = kTrace ? ah : fmaR(R(-0.5), dT, ah);
+        if constexpr (kCentral) {
+            const R eh = kTrace ? -ah : tq - ah;
+            dh[1] = eh - xh;
+            dh[3] = eh + xh;
+            dh[2] = eh - yh;
+            dh[4] = eh + yh;
+        } else {
+            dh[1] = kTrace ? -(xh + ah) : tq - (xh + ah);
+            dh[3] = kTrace ? xh - ah : tq + (xh - ah);
+            dh[2] = kTrace ? -(yh + ah) : tq - (yh + ah);
+            dh[4] = kTrace ? yh - ah : tq + (yh - ah);
+        }
         const R hp = xh + yh, hm = xh - yh;
         dh[5] = ah + hp;
         dh[7] = ah - hp;
         dh[6] = ah - hm;
         dh[8] = ah + hm;
-        if constexpr (kTrace) {
-            dh[0] = R(4) * ah;
-            dh[1] = R(-2) * (xh + ah);
-            dh[3] = R(2) * (xh - ah);
-            dh[2] = R(-2) * (yh + ah);
-            dh[4] = R(2) * (yh - ah);
-        } else {
-            const R th = R(0.25) * dT;
-            dh[0] = fmaR(R(4), ah, -dT);
-            dh[1] = fmaR(R(-2), xh + ah, th);
-            dh[3] = fmaR(R(2), xh - ah, th);
-            dh[2] = fmaR(R(-2), yh + ah, th);
-            dh[4] = fmaR(R(2), yh - ah, th);
-        }
     }
 
     if constexpr (GM == GFIX) {
@@ -367,35 +371,76 @@ __device__ __forceinline__ void kbc_forward(const R (&g)[9], const Coef<R>& K, K
         n.b = R(1);
     } else {
         // entropic scalar products, weights 1 / (W_i (1 + e_i)) = rho / feq_i;
-        // d_i = W_i (1 + e_i) = W_i (1 - 1.5 |u|^2 + 4.5 (v.u)^2) + 3 W_i (v.u)
+        // d_i = W_i (1 + e_i) = W_i (1 - 1.5 |u|^2 + 4.5 (v.u)^2) + 3 W_i (v.u),
+        // a quarter of it for the rest population and four times for the diagonals
+        const R upv = ux + uy, umv = ux - uy;
         const R a1 = fmaR(R(-1.0 / 6.0), u2, R(1.0 / 9.0));
-        const R a5 = fmaR(R(1.0 / 12.0), u2, R(1.0 / 36.0));
-        const R dx = fmaR(R(0.5), uxx, a1), dy = fmaR(R(0.5), uyy, a1);
-        const R dp = fmaR(R(0.25), uxy, a5), dm = fmaR(R(-0.25), uxy, a5);
+        const R b1 = fmaR(R(1.0 / 3.0), u2, R(1.0 / 9.0));
+        const R uxy = ux * uy;
+        const R dx = fmaR(R(0.5), uxx, a1), dy = kCentral ? fmaR(R(-0.5), uxx, b1) : fmaR(R(0.5), uyy, a1);
+        const R dp = kCentral ? fmaR(ux, uy, b1) : b1 + uxy, dm = kCentral ? fmaR(-ux, uy, b1) : b1 - uxy;
         R d[9];
-        d[0] = fmaR(R(-2.0 / 3.0), u2, R(4.0 / 9.0));
+        d[0] = a1;
         d[1] = fmaR(R(1.0 / 3.0), ux, dx);
         d[3] = fmaR(R(-1.0 / 3.0), ux, dx);
         d[2] = fmaR(R(1.0 / 3.0), uy, dy);
         d[4] = fmaR(R(-1.0 / 3.0), uy, dy);
-        d[5] = fmaR(R(1.0 / 12.0), upv, dp);
-        d[7] = fmaR(R(-1.0 / 12.0), upv, dp);
-        d[8] = fmaR(R(1.0 / 12.0), umv, dm);
-        d[6] = fmaR(R(-1.0 / 12.0), umv, dm);
-        R a = R(0), b = R(0), c = R(0);
+        d[5] = fmaR(R(1.0 / 3.0), upv, dp);
+        d[7] = fmaR(R(-1.0 / 3.0), upv, dp);
+        d[8] = fmaR(R(1.0 / 3.0), umv, dm);
+        d[6] = fmaR(R(-1.0 / 3.0), umv, dm);
+        R a = R(0), b = R(0);
+        R wh[9];
 #pragma unroll
         for (int i = 0; i < 9; ++i) {
             n.w[i] = rcpR(d[i]);
-            const R wh = dh[i] * n.w[i];
-            a = fmaR(ds[i], wh, a);
-            b = fmaR(dh[i], wh, b);
-            c = fmaR(ds[i] * n.w[i], ds[i], c);
+            wh[i] = dh[i] * n.w[i];
+            b = i ? fmaR(dh[i], wh[i], b) : dh[i] * wh[i];
+            if (VAR != VD || i) a = (i == (VAR == VD ? 1 : 0)) ? ds[i] * wh[i] : fmaR(ds[i], wh[i], a);
         }
         n.ratio = divR(a, b);
         n.b = b;
         const R gs = fmaR(-K.two_m_inv_beta, n.ratio, K.inv_beta);
-        n.active = !(b <= K.guard * c);
+        // the guard, eq. (result21) only where <dh|dh> > guard <ds|ds>
+        if constexpr (kCentral) {
+            // <ds|ds> (18 instructions) is formed by the waves that hold a
+            // node where its bound does not decide (or a NaN)
+            R m = fmaR(dP, dP, dN * dN);
+            if constexpr (kTrace) m = fmaR(dT, dT, m);
+            n.active = true;
+            if (!(b > (guard_bound<R>() * K.guard) * m && u2 < R(1.0 / 6.0))) {
+                R c = R(0);
+#pragma unroll
+                for (int i = 0; i < 9; ++i) c = fmaR(ds[i] * n.w[i], ds[i], c);
+                n.active = !(b <= K.guard * c);
+            }
+        } else {
+            // populations of ds that differ in sign only are summed by their weights
+            const R wd = (n.w[5] + n.w[7]) + (n.w[6] + n.w[8]);
+            const R wx = n.w[1] + n.w[3], wy = n.w[2] + n.w[4];
+            R c;
+            if constexpr (kTrace) {
+                c = fmaR(p2 * p2, wd, fmaR(tpn * tpn, wx, (tmn * tmn) * wy));
+                c = fmaR(ds[0] * n.w[0], ds[0], c);
+            } else {
+                c = fmaR(p2 * p2, wd, (n4 * n4) * (wx + wy));
+            }
+            n.active = !(b <= K.guard * c);
+        }
         n.gam = n.active ? gs : R(2);
+    }
+}
+
+// ds, dh and w of a node in their own units.
+template <typename R>
+__device__ __forceinline__ void unscaled(const KbcNode<R>& n, R (&ds)[9], R (&dh)[9], R (&w)[9]) {
+#pragma unroll
+    for (int i = 0; i < 9; ++i) {
+        constexpr R one = R(1);
+        const R k = one / node_scale<R>(i), k2 = node_scale<R>(i) * node_scale<R>(i);
+        ds[i] = (i == 0 || i > 4) ? n.ds[i] * k : n.ds[i];
+        dh[i] = (i == 0 || i > 4) ? n.dh[i] * k : n.dh[i];
+        w[i] = (i == 0 || i > 4) ? n.w[i] * k2 : n.w[i];
     }
 }
 
@@ -442,12 +487,22 @@ __device__ __forceinline__ R collide(R (&g)[9], const Coef<R>& K) {
         kbc_forward<R, VAR, (GM == GEXACT ? GEST : GM)>(g, K, n);
         R gam = n.gam;
         if constexpr (GM == GEXACT) {
-            if (n.active) gam = exact_gamma<R>(gam, n.ds, n.dh, n.w, n.ir, K);
+            if (n.active) {
+                R ds[9], dh[9], w[9];
+                unscaled(n, ds, dh, w);
+                gam = exact_gamma<R>(gam, ds, dh, w, n.ir, K);
+            }
         }
         // f' = f - beta (2 ds + gamma dh), eqs. (Egeneral), (ksh-mirror)
-        const R tb = R(2) * K.beta, bg = K.beta * gam;
+        const R tb[3] = {R(4) * K.beta, R(2) * K.beta, K.beta};
+        const R bg[3] = {(R(2) * K.beta) * gam, K.beta * gam, (R(0.5) * K.beta) * gam};
 #pragma unroll
-        for (int i = 0; i < 9; ++i) g[i] = fmaR(-bg, n.dh[i], fmaR(-tb, n.ds[i], g[i]));
+        for (int i = 0; i < 9; ++i) {
+            const int k = i == 0 ? 0 : (i < 5 ? 1 : 2);
+            // D has no shear part in the rest population
+            const R t = (VAR == VD && i == 0) ? g[0] : fmaR(-tb[k], n.ds[i], g[i]);
+            g[i] = fmaR(-bg[k], n.dh[i], t);
+        }
         return gam;
     }
 }
