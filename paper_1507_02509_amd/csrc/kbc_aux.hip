@@ -5,6 +5,7 @@
 // population f_i(x, t = n) sits in population row i of lattice row y - v_iy,
 // at column x - v_ix ([ny][9][pitch] layout).
 #include "kbc_launch.hpp"
+#include "kbc_tile2.hpp"
 
 namespace kbc {
 
@@ -175,105 +176,210 @@ __device__ __forceinline__ void block_store(double (&acc)[CNT], double* partials
     }
 }
 
-template <int FORM, int COLL, int VAR, int GM>
-__global__ __launch_bounds__(256) void k_diag_a(const typename Form<FORM>::S* __restrict__ src, int nx,
-                                                int ny, int64_t pitch, Coef<typename Form<FORM>::R> K,
-                                                double rho0, double* __restrict__ ux_s,
-                                                double* __restrict__ uy_s, double* __restrict__ partials) {
+// ln(f / W) for f / W in [1/2, 2], from s = (f - W) / (f + W): 2 atanh(s) =
+// 2 s P(s^2), P the polynomial of degree 10 with the smallest largest relative
+// error on s^2 <= 1/9 (1.3e-18; coefficients by Remez's exchange algorithm).
+// 17 FP64 instructions, against about 100 for the library logarithm and 11 for
+// the division f / W; and as f - W is formed from the stored deviation, no
+// digits of a small deviation are lost.
+__device__ __forceinline__ double atanh_poly(double z) {
+    double p = 0.08504923007075064;
+    p = fmaR(z, p, 0.04172462195061191);
+    p = fmaR(z, p, 0.06052477641340325);
+    p = fmaR(z, p, 0.06650560071689546);
+    p = fmaR(z, p, 0.07693274239195039);
+    p = fmaR(z, p, 0.09090872237804135);
+    p = fmaR(z, p, 0.11111111976861492);
+    p = fmaR(z, p, 0.14285714274058622);
+    p = fmaR(z, p, 0.20000000000077559);
+    p = fmaR(z, p, 0.33333333333333154);
+    return fmaR(z, p, 1.0);
+}
+
+// u = j / r to within an ulp: one refined reciprocal of the density and a
+// correction step per component (11 instructions); the library division, 11
+// instructions each, where the density is too small or large for that (or not
+// finite).
+__device__ __forceinline__ void velocity(double jx, double jy, double r, double& u, double& v) {
+    const double ar = fabs(r);
+    if (ar > 1e-150 && ar < 1e150) {
+        const double ir = rcpR(r), a = jx * ir, b = jy * ir;
+        u = fmaR(fmaR(-r, a, jx), ir, a);
+        v = fmaR(fmaR(-r, b, jy), ir, b);
+    } else {
+        u = jx / r;
+        v = jy / r;
+    }
+}
+
+// All statistics of the state in one pass.  Bound by FP64 vector issue (about
+// 600 instructions per node, 200 of them the nine logarithms); the state is
+// read once (1.3 times through L2) and nothing but the sums is written.
+//
+// A workgroup takes 64 x TH tiles of its XCD's band in turn.  The
+// vorticity at a node needs the velocity one node away and the palinstrophy
+// the vorticity one node away, so the velocity is formed on the tile extended
+// by two nodes on every side and the vorticity on one, both kept in LDS; the
+// previous three passes instead wrote and re-read both fields in memory
+// (2048^2 FP32 KBC-D: 228 us for the call, 99 with one pass).  Rows of 64 nodes
+// are one wave each (uniform row, scalar bases); the four columns beside the
+// tile are lanes of their own.
+template <int FORM, int COLL, int VAR, int GM, int TH>
+__global__ __launch_bounds__(256) void k_diag(const typename Form<FORM>::S* __restrict__ src, int nx, int ny,
+                                              int64_t pitch, Coef<typename Form<FORM>::R> K, double rho0, int ntx,
+                                              int ntiles, double* __restrict__ partials) {
     using F = Form<FORM>;
     using R = typename F::R;
-    const int64_t N = static_cast<int64_t>(nx) * ny;
-    double acc[11] = {0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0};
-    for (int64_t n = static_cast<int64_t>(blockIdx.x) * 256 + threadIdx.x; n < N;
-         n += static_cast<int64_t>(gridDim.x) * 256) {
-        const int y = static_cast<int>(n / nx), x = static_cast<int>(n - static_cast<int64_t>(y) * nx);
-        typename F::S s[9];
+    using S = typename F::S;
+    constexpr int TW = 64, EW = TW + 4, EH = TH + 4;
+    __shared__ double su[EH][EW], sv[EH][EW], sw[TH + 2][TW + 2];
+    const int lane = static_cast<int>(threadIdx.x & 63u);
+    const int w = __builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x >> 6));
+    double acc[15] = {0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0};
+
+    const int per_xcd = (ntiles + 7) >> 3, nwg = static_cast<int>(gridDim.x >> 3);
+    const int band0 = static_cast<int>(blockIdx.x & 7u) * per_xcd;
+    const int band1 = (band0 + per_xcd < ntiles) ? band0 + per_xcd : ntiles;
+    for (int t = band0 + static_cast<int>(blockIdx.x >> 3); t < band1; t += nwg) {
+        const int ty = t / ntx;
+        const int x0 = (t - ty * ntx) * TW, y0 = ty * TH;
+        // velocity on the extended tile; the other sums on the tile's own nodes
+        const int gx = pmod(x0 + lane, nx);
+        const int gxm = gx == 0 ? nx - 1 : gx - 1, gxp = gx == nx - 1 ? 0 : gx + 1;
+        for (int ey = w; ey < EH; ey += 4) {
+            const int yy = y0 - 2 + ey;
+            const int y = wrap_uniform(yy, ny), ym = y == 0 ? ny - 1 : y - 1, yp = y == ny - 1 ? 0 : y + 1;
+            const uint32_t c0 = static_cast<uint32_t>(gx) * sizeof(S), cm = static_cast<uint32_t>(gxm) * sizeof(S),
+                           cp = static_cast<uint32_t>(gxp) * sizeof(S);
+            S s[9];
+            s[0] = ld_at(row_ptr(src, y, 0, pitch), c0);
+            s[1] = ld_at(row_ptr(src, y, 1, pitch), cm);
+            s[2] = ld_at(row_ptr(src, ym, 2, pitch), c0);
+            s[3] = ld_at(row_ptr(src, y, 3, pitch), cp);
+            s[4] = ld_at(row_ptr(src, yp, 4, pitch), c0);
+            s[5] = ld_at(row_ptr(src, ym, 5, pitch), cm);
+            s[6] = ld_at(row_ptr(src, ym, 6, pitch), cp);
+            s[7] = ld_at(row_ptr(src, yp, 7, pitch), cp);
+            s[8] = ld_at(row_ptr(src, yp, 8, pitch), cm);
+            double q[9], dr = 0.0, jx = 0.0, jy = 0.0;
 #pragma unroll
-        for (int i = 0; i < 9; ++i) s[i] = src[src_off(i, x, y, nx, ny, pitch)];
-        double f[9], dr = 0.0, jx = 0.0, jy = 0.0;
-        bool finite = true;
+            for (int i = 0; i < 9; ++i) {
+                q[i] = F::dec64(s[i], i);
+                dr += q[i];
+                if (kCx[i]) jx += kCx[i] * q[i];
+                if (kCy[i]) jy += kCy[i] * q[i];
+            }
+            const double r = rho0 + dr;
+            double u, v;
+            velocity(jx, jy, r, u, v);
+            su[ey][lane + 2] = u;
+            sv[ey][lane + 2] = v;
+            if (ey < 2 || ey >= TH + 2 || yy >= ny || x0 + lane >= nx) continue;
+            const double u2 = u * u + v * v;
+            // entropy -sum f ln(f / W): the general form where a population is
+            // beyond a factor two of its weight (or not finite: then dr is not)
+            double Sn = 0.0, zmax = 0.0;
 #pragma unroll
-        for (int i = 0; i < 9; ++i) {
-            const double g = F::dec64(s[i], i);
-            f[i] = g + weight(i) * rho0;
-            finite = finite && isfinite(f[i]);
-            dr += g;
-            jx += kCx[i] * g;
-            jy += kCy[i] * g;
+            for (int i = 0; i < 9; ++i) {
+                const double num = q[i] + weight(i) * (rho0 - 1.0), den = q[i] + weight(i) * (rho0 + 1.0);
+                const double a = num * rcpR(den), z = a * a;
+                zmax = fmax(zmax, z);
+                Sn = fmaR(q[i] + weight(i) * rho0, -2.0 * a * atanh_poly(z), Sn);
+            }
+            const bool sum_finite = isfinite(dr);
+            bool finite = true;
+            if (!(sum_finite && zmax <= 1.0 / 9.0)) {
+                Sn = 0.0;
+#pragma unroll
+                for (int i = 0; i < 9; ++i) {
+                    const double f = q[i] + weight(i) * rho0;
+                    finite = finite && isfinite(f);
+                    Sn -= f * log(f / weight(i));
+                }
+            }
+            // some feq_i <= 0 (or NaN): none where rho > 0 and |u|^2 < 1/6,
+            // as 1 + e_i >= 1/2 - 1.5 |u|^2
+            bool neg = false;
+            if (!(r > 0.0 && u2 < 1.0 / 6.0)) {
+#pragma unroll
+                for (int i = 0; i < 9; ++i) {
+                    const double cu = kCx[i] * u + kCy[i] * v;
+                    const double feq = weight(i) * r * (1.0 + 3.0 * cu + 4.5 * cu * cu - 1.5 * u2);
+                    neg = neg || !(feq > 0.0);
+                }
+            }
+            R g[9];
+#pragma unroll
+            for (int i = 0; i < 9; ++i) g[i] = F::dec(s[i], i);
+            const double gm = static_cast<double>(collide<R, COLL, VAR, GM>(g, K));
+            const double e = 0.5 * u2;
+            acc[0] += r;
+            acc[1] += jx;
+            acc[2] += jy;
+            acc[3] += e;
+            acc[4] = fmaR(e, e, acc[4]);
+            acc[5] += Sn;
+            acc[6] += gm;
+            acc[7] = fmaR(gm, gm, acc[7]);
+            acc[8] += finite ? 0.0 : 1.0;
+            acc[9] += neg ? 1.0 : 0.0;
+            acc[10] = fmaR(r, r, acc[10]);
         }
-        const double r = rho0 + dr;
-        const double u = jx / r, v = jy / r;
-        ux_s[n] = u;
-        uy_s[n] = v;
-        double Sn = 0.0;
-        bool neg = false;
-        const double u2 = u * u + v * v;
+        // the two columns on each side
+        for (int k = static_cast<int>(threadIdx.x); k < 4 * EH; k += 256) {
+            const int ey = k >> 2, c = k & 3;
+            const int ex = c < 2 ? c : TW + c;
+            const int x = pmod(x0 - 2 + ex, nx), y = pmod(y0 - 2 + ey, ny);
+            double dr = 0.0, jx = 0.0, jy = 0.0;
 #pragma unroll
-        for (int i = 0; i < 9; ++i) {
-            Sn -= f[i] * log(f[i] / weight(i));
-            const double cu = kCx[i] * u + kCy[i] * v;
-            const double feq = weight(i) * r * (1.0 + 3.0 * cu + 4.5 * cu * cu - 1.5 * u2);
-            neg = neg || !(feq > 0.0);
+            for (int i = 0; i < 9; ++i) {
+                const double q = F::dec64(src[src_off(i, x, y, nx, ny, pitch)], i);
+                dr += q;
+                if (kCx[i]) jx += kCx[i] * q;
+                if (kCy[i]) jy += kCy[i] * q;
+            }
+            velocity(jx, jy, rho0 + dr, su[ey][ex], sv[ey][ex]);
         }
-        R g[9];
-#pragma unroll
-        for (int i = 0; i < 9; ++i) g[i] = F::dec(s[i], i);
-        const double gm = static_cast<double>(collide<R, COLL, VAR, GM>(g, K));
-        const double e = 0.5 * u2;
-        acc[0] += r;
-        acc[1] += jx;
-        acc[2] += jy;
-        acc[3] += e;
-        acc[4] += e * e;
-        acc[5] += Sn;
-        acc[6] += gm;
-        acc[7] += gm * gm;
-        acc[8] += finite ? 0.0 : 1.0;
-        acc[9] += neg ? 1.0 : 0.0;
-        acc[10] += r * r;
+        __syncthreads();
+        // vorticity on the tile and one node around it
+        for (int k = static_cast<int>(threadIdx.x); k < (TH + 2) * (TW + 2); k += 256) {
+            const int r = k / (TW + 2), c = k - r * (TW + 2);
+            sw[r][c] = 0.5 * (sv[r + 1][c + 2] - sv[r + 1][c]) - 0.5 * (su[r + 2][c + 1] - su[r][c + 1]);
+        }
+        __syncthreads();
+        for (int oy = w; oy < TH; oy += 4) {
+            if (y0 + oy >= ny || x0 + lane >= nx) continue;
+            const double om = sw[oy + 1][lane + 1];
+            const double z = 0.5 * om * om;
+            const double hx = 0.5 * (sw[oy + 1][lane + 2] - sw[oy + 1][lane]);
+            const double hy = 0.5 * (sw[oy + 2][lane + 1] - sw[oy][lane + 1]);
+            const double p = 0.5 * (hx * hx + hy * hy);
+            acc[11] += z;
+            acc[12] = fmaR(z, z, acc[12]);
+            acc[13] += p;
+            acc[14] = fmaR(p, p, acc[14]);
+        }
+        // the next tile writes su, sv after every wave is past the vorticity
+        // (the barrier above) and sw after the next tile's first barrier
     }
-    block_store<11>(acc, partials, D_RHO);
+    block_store<15>(acc, partials, 0);
 }
 
-__global__ __launch_bounds__(256) void k_diag_b(int nx, int ny, const double* __restrict__ ux_s,
-                                                const double* __restrict__ uy_s, double* __restrict__ w_s,
-                                                double* __restrict__ partials) {
-    const int64_t N = static_cast<int64_t>(nx) * ny;
-    double acc[2] = {0, 0};
-    for (int64_t n = static_cast<int64_t>(blockIdx.x) * 256 + threadIdx.x; n < N;
-         n += static_cast<int64_t>(gridDim.x) * 256) {
-        const int y = static_cast<int>(n / nx), x = static_cast<int>(n - static_cast<int64_t>(y) * nx);
-        const int64_t xp = static_cast<int64_t>(y) * nx + wrap(x + 1, nx);
-        const int64_t xm = static_cast<int64_t>(y) * nx + wrap(x - 1, nx);
-        const int64_t yp = static_cast<int64_t>(wrap(y + 1, ny)) * nx + x;
-        const int64_t ym = static_cast<int64_t>(wrap(y - 1, ny)) * nx + x;
-        const double w = 0.5 * (uy_s[xp] - uy_s[xm]) - 0.5 * (ux_s[yp] - ux_s[ym]);
-        w_s[n] = w;
-        const double z = 0.5 * w * w;
-        acc[0] += z;
-        acc[1] += z * z;
+// out[k] = sum over the kDiagBlocks partials of slot k, in a fixed order: one
+// workgroup of kDiagSlots threads per group of blocks, then across the groups
+__global__ __launch_bounds__(1024) void k_diag_sum(const double* __restrict__ partials, double* __restrict__ out) {
+    constexpr int kGroups = 1024 / kDiagSlots;
+    __shared__ double red[kGroups][kDiagSlots];
+    const int k = static_cast<int>(threadIdx.x) % kDiagSlots, g = static_cast<int>(threadIdx.x) / kDiagSlots;
+    double s = 0.0;
+    for (int b = g; k != D_UNUSED && b < kDiagBlocks; b += kGroups) s += partials[static_cast<int64_t>(b) * kDiagSlots + k];
+    red[g][k] = s;
+    __syncthreads();
+    if (g == 0) {
+        double t = 0.0;
+        for (int j = 0; j < kGroups; ++j) t += red[j][k];
+        out[k] = t;
     }
-    block_store<2>(acc, partials, D_Z);
-}
-
-__global__ __launch_bounds__(256) void k_diag_c(int nx, int ny, const double* __restrict__ w_s,
-                                                double* __restrict__ partials) {
-    const int64_t N = static_cast<int64_t>(nx) * ny;
-    double acc[2] = {0, 0};
-    for (int64_t n = static_cast<int64_t>(blockIdx.x) * 256 + threadIdx.x; n < N;
-         n += static_cast<int64_t>(gridDim.x) * 256) {
-        const int y = static_cast<int>(n / nx), x = static_cast<int>(n - static_cast<int64_t>(y) * nx);
-        const int64_t xp = static_cast<int64_t>(y) * nx + wrap(x + 1, nx);
-        const int64_t xm = static_cast<int64_t>(y) * nx + wrap(x - 1, nx);
-        const int64_t yp = static_cast<int64_t>(wrap(y + 1, ny)) * nx + x;
-        const int64_t ym = static_cast<int64_t>(wrap(y - 1, ny)) * nx + x;
-        const double gx = 0.5 * (w_s[xp] - w_s[xm]);
-        const double gy = 0.5 * (w_s[yp] - w_s[ym]);
-        const double p = 0.5 * (gx * gx + gy * gy);
-        acc[0] += p;
-        acc[1] += p * p;
-    }
-    block_store<2>(acc, partials, D_P);
 }
 
 // ------------------------------------------------------------ copy reference
@@ -305,16 +411,25 @@ struct MomOp {
 
 template <int FORM, int COLL, int VAR, int GM>
 struct DiagOp {
-    static int run(const Lattice& L, const void* src, double* ux_s, double* uy_s, double* w_s,
-                   double* partials) {
+    template <int TH>
+    static int go(const Lattice& L, const void* src, double* partials) {
         using F = Form<FORM>;
-        k_diag_a<FORM, COLL, VAR, GM><<<kDiagBlocks, 256, 0, L.stream>>>(
-            static_cast<const typename F::S*>(src), L.nx, L.ny, L.pitch, make_coef<typename F::R>(L),
-            L.rho0, ux_s, uy_s, partials);
-        if (ok_launch()) return -2;
-        k_diag_b<<<kDiagBlocks, 256, 0, L.stream>>>(L.nx, L.ny, ux_s, uy_s, w_s, partials);
-        if (ok_launch()) return -2;
-        k_diag_c<<<kDiagBlocks, 256, 0, L.stream>>>(L.nx, L.ny, w_s, partials);
+        const int ntx = (L.nx + 63) / 64;
+        const int64_t ntiles = static_cast<int64_t>(ntx) * ((L.ny + TH - 1) / TH);
+        if (ntiles > kMaxDiagTiles) return kTooLarge;
+        k_diag<FORM, COLL, VAR, GM, TH><<<kDiagBlocks, 256, 0, L.stream>>>(
+            static_cast<const typename F::S*>(src), L.nx, L.ny, L.pitch, make_coef<typename F::R>(L), L.rho0, ntx,
+            static_cast<int>(ntiles), partials);
+        return ok_launch();
+    }
+    // 16-row tiles (a quarter more velocities than nodes) where they give
+    // every workgroup of the grid one; 8-row tiles below that, where the
+    // length of a workgroup's row loop is the time
+    static int run(const Lattice& L, const void* src, double* partials, double* out) {
+        const int64_t tiles16 = static_cast<int64_t>((L.nx + 63) / 64) * ((L.ny + 15) / 16);
+        const int rc = tiles16 >= kDiagBlocks ? go<16>(L, src, partials) : go<8>(L, src, partials);
+        if (rc) return rc;
+        k_diag_sum<<<1, 1024, 0, L.stream>>>(partials, out);
         return ok_launch();
     }
 };
@@ -359,9 +474,8 @@ int launch_set_pop(const Lattice& L, void* dst, const double* f) {
     return ok_launch();
 }
 
-int launch_diag(const Lattice& L, const void* src, double* ux_s, double* uy_s, double* w_s,
-                double* partials) {
-    return dispatch<DiagOp>(L, src, ux_s, uy_s, w_s, partials);
+int launch_diag(const Lattice& L, const void* src, double* partials, double* out) {
+    return dispatch<DiagOp>(L, src, partials, out);
 }
 
 int launch_copy(void* dst, const void* src, size_t n_words, hipStream_t stream) {

@@ -25,8 +25,8 @@ struct lbm_ctx {
     kbc::StepShape shape;
     int fuse;               // time steps per launch of lbm_step: 1 or 2
     int fuse_rows;          // output tile height of the fused launch: 8, 16, 24 or 32
-    double* dscratch;       // ux, uy, omega fields + diagnostics partials
-    size_t dscratch_elems;
+    double* dscratch;       // diagnostics: block partials (device)
+    double* dresult;        // diagnostics: sums (pinned host memory the kernel writes)
     double* ascratch;       // adjoint: block partials + initial-state stencil fields
     size_t ascratch_elems;
     double* sscratch;       // spectra: velocity fields and their transforms
@@ -194,7 +194,7 @@ int lbm_init(lbm_ctx** out, const lbm_params* p, void* buf_a, void* buf_b, size_
     // FP16 alike)
     if (static_cast<int64_t>((p->nx + 63) / 64) * ((p->ny + 15) / 16) < 1792) c->fuse_rows = 8;
     c->dscratch = nullptr;
-    c->dscratch_elems = 0;
+    c->dresult = nullptr;
     c->ascratch = nullptr;
     c->ascratch_elems = 0;
     c->sscratch = nullptr;
@@ -379,37 +379,27 @@ int lbm_set_populations(lbm_ctx* c, const double* f) {
 
 int lbm_diagnostics(lbm_ctx* c, lbm_diag* out) {
     if (!c || !out) return fail(LBM_EINVAL, "ctx and out must not be NULL");
-    const size_t N = static_cast<size_t>(c->p.nx) * c->p.ny;
-    const size_t need = 3 * N + static_cast<size_t>(kbc::kDiagBlocks) * kbc::kDiagSlots;
-    if (c->dscratch_elems < need) {
-        if (c->dscratch) {
-            hipError_t e = hipStreamSynchronize(c->L.stream);
-            if (e != hipSuccess) return hip_fail(e, "lbm_diagnostics sync");
-            (void)hipFree(c->dscratch);
-            c->dscratch = nullptr;
-            c->dscratch_elems = 0;
-        }
-        hipError_t e = hipMalloc(&c->dscratch, need * sizeof(double));
+    if (!c->dscratch) {
+        hipError_t e = hipMalloc(&c->dscratch, sizeof(double) * kbc::kDiagBlocks * kbc::kDiagSlots);
         if (e != hipSuccess) {
             c->dscratch = nullptr;
             return fail(LBM_ENOMEM, "diagnostics scratch: %s", hipGetErrorString(e));
         }
-        c->dscratch_elems = need;
     }
-    double* ux_s = c->dscratch;
-    double* uy_s = ux_s + N;
-    double* w_s = uy_s + N;
-    double* part = w_s + N;
-    int rc = kbc::launch_diag(c->L, c->buf[c->cur], ux_s, uy_s, w_s, part);
+    if (!c->dresult) {
+        hipError_t e = hipHostMalloc(&c->dresult, sizeof(double) * kbc::kDiagSlots, hipHostMallocDefault);
+        if (e != hipSuccess) {
+            c->dresult = nullptr;
+            return fail(LBM_ENOMEM, "diagnostics result: %s", hipGetErrorString(e));
+        }
+    }
+    // the sums are written straight to host memory: no copy to enqueue
+    int rc = kbc::launch_diag(c->L, c->buf[c->cur], c->dscratch, c->dresult);
     if (rc) return launch_result(rc, "lbm_diagnostics");
-    std::vector<double> h(static_cast<size_t>(kbc::kDiagBlocks) * kbc::kDiagSlots);
-    hipError_t e = hipMemcpyAsync(h.data(), part, h.size() * sizeof(double), hipMemcpyDeviceToHost, c->L.stream);
-    if (e != hipSuccess) return hip_fail(e, "lbm_diagnostics copy");
-    e = hipStreamSynchronize(c->L.stream);
+    hipError_t e = hipStreamSynchronize(c->L.stream);
     if (e != hipSuccess) return hip_fail(e, "lbm_diagnostics sync");
-    double s[kbc::kDiagSlots] = {0};
-    for (int b = 0; b < kbc::kDiagBlocks; ++b)
-        for (int k = 0; k < kbc::kDiagSlots; ++k) s[k] += h[static_cast<size_t>(b) * kbc::kDiagSlots + k];
+    const double* s = c->dresult;
+    const size_t N = static_cast<size_t>(c->p.nx) * c->p.ny;
     const double n = static_cast<double>(N);
     auto sd = [n](double sum, double sum2) {
         const double m = sum / n;
@@ -493,6 +483,7 @@ int lbm_free(lbm_ctx* c) {
             if (c->gexec[k]) (void)hipGraphExecDestroy(c->gexec[k]);
         if (c->cap_stream) (void)hipStreamDestroy(c->cap_stream);
         if (c->dscratch) (void)hipFree(c->dscratch);
+        if (c->dresult) (void)hipHostFree(c->dresult);
         if (c->ascratch) (void)hipFree(c->ascratch);
         if (c->sscratch) (void)hipFree(c->sscratch);
         kbc::destroy_spectra_plan(c->fft_plan);

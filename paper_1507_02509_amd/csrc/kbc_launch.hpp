@@ -60,11 +60,13 @@ int launch_moments(const Lattice& L, const void* src, double* rho, double* ux, d
 int launch_get_pop(const Lattice& L, const void* src, double* f);
 int launch_set_pop(const Lattice& L, void* dst, const double* f);
 
-// diagnostics: three passes writing per-block FP64 partials (kDiagSlots each)
+// diagnostics: one pass over the state writing kDiagBlocks rows of kDiagSlots
+// FP64 partials, and their sums (fixed order) to out[kDiagSlots], which may be
+// host memory the device can write
 constexpr int kDiagSlots = 16;
-constexpr int kDiagBlocks = 1024;
-int launch_diag(const Lattice& L, const void* src, double* ux_s, double* uy_s, double* w_s,
-                double* partials);
+constexpr int kDiagBlocks = 1024;   // four workgroups per CU, a multiple of 8
+constexpr int64_t kMaxDiagTiles = (int64_t{1} << 31) - 1 - kDiagBlocks;
+int launch_diag(const Lattice& L, const void* src, double* partials, double* out);
 
 int launch_copy(void* dst, const void* src, size_t n_words, hipStream_t stream);
 
