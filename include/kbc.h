@@ -188,9 +188,11 @@ int lbm_set_step(lbm_ctx* c, int64_t n);
  * Z_k[s] = the same sum weighted by (2 pi |k| / N)^2 (enstrophy with the
  * exact derivative, so it differs from the diagnostics' central-difference
  * Z at high k).  E_k and Z_k are device arrays of kmax + 1 doubles (either may
- * be NULL); shells above kmax are dropped.  Shell sums use atomic adds:
- * repeatable to rounding, not bit for bit.  Allocates 2 N^2 + 4 N (N/2 + 1)
- * doubles of scratch and an FFT plan on first use (kept until lbm_free).
+ * be NULL); shells above kmax are dropped.  A shell's sum is formed in no
+ * fixed order: repeatable to rounding, not bit for bit.  Allocates
+ * 4 N (N/2 + 1) doubles of scratch, 532 more for every 256 x 8 of the
+ * (N/2 + 1)^2 wavevectors of a quadrant, and an FFT plan on first use (kept
+ * until lbm_free).
  * LBM_EUNSUPPORTED for non-square lattices. */
 int lbm_spectra(lbm_ctx* c, int32_t kmax, double* E_k, double* Z_k);
 

@@ -497,8 +497,7 @@ int lbm_spectra(lbm_ctx* c, int32_t kmax, double* E_k, double* Z_k) {
     if (c->p.nx != c->p.ny) return fail(LBM_EUNSUPPORTED, "spectra need a square lattice (%d x %d)", c->p.nx, c->p.ny);
     if (kmax < 0) return fail(LBM_EINVAL, "kmax must be >= 0");
     if (!E_k && !Z_k) return LBM_OK;
-    const size_t n = static_cast<size_t>(c->p.nx);
-    const size_t need = 2 * n * n + 4 * n * (n / 2 + 1);
+    const size_t need = static_cast<size_t>(kbc::spectra_work(c->p.nx));
     if (c->sscratch_elems < need) {
         if (c->sscratch) {
             hipError_t e = hipStreamSynchronize(c->L.stream);
