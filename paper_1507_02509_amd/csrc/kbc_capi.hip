@@ -25,6 +25,7 @@ struct lbm_ctx {
     kbc::StepShape shape;
     int fuse;               // time steps per launch of lbm_step: 1 or 2
     int fuse_rows;          // output tile height of the fused launch: 8, 16, 24 or 32
+    int default_rows;       // its default for this lattice
     double* dscratch;       // diagnostics: block partials (device)
     double* dresult;        // diagnostics: sums (pinned host memory the kernel writes)
     double* ascratch;       // adjoint: block partials + initial-state stencil fields
@@ -193,6 +194,7 @@ int lbm_init(lbm_ctx** out, const lbm_params* p, void* buf_a, void* buf_b, size_
     // 512^2 3.7 / 4.2, 1152^2 11.5 / 12.1, 1280^2 13.5 / 14.1, 1408^2 a tie;
     // FP16 alike)
     if (static_cast<int64_t>((p->nx + 63) / 64) * ((p->ny + 15) / 16) < 1792) c->fuse_rows = 8;
+    c->default_rows = c->fuse_rows;
     c->dscratch = nullptr;
     c->dresult = nullptr;
     c->ascratch = nullptr;
@@ -225,6 +227,21 @@ namespace {
 // index and step counter advanced as they are enqueued.
 int step_eager(lbm_ctx* c, int32_t nsteps) {
     int32_t s = 0;
+    // Four steps per launch where that pays, unless the caller has chosen
+    // another fused tile.  An even number of such launches: each takes the
+    // place of two launches of two steps, so the state ends in the same buffer
+    // as without them (an ensemble's members must agree on it).
+    const int shape4 = (c->fuse == 2 && c->fuse_rows == c->default_rows && nsteps >= 8)
+                           ? kbc::step4_shape(c->L, c->shape.nt) : 0;
+    if (shape4) {
+        for (; s + 8 <= nsteps; s += 8)
+            for (int k = 0; k < 2; ++k) {
+                const int rc = kbc::launch_step4(c->L, c->buf[c->cur], c->buf[c->cur ^ 1], shape4, c->shape.nt);
+                if (rc) return launch_result(rc, "lbm_step (four fused steps)");
+                c->cur ^= 1;
+                c->steps += 4;
+            }
+    }
     if (c->fuse == 2) {
         for (; s + 2 <= nsteps; s += 2) {
             const int rc = kbc::launch_step2(c->L, c->buf[c->cur], c->buf[c->cur ^ 1], c->fuse_rows, c->shape.nt);

@@ -53,6 +53,11 @@ int launch_step(const Lattice& L, const void* src, void* dst, const StepShape& s
 // two fused steps src -> dst (kbc_step2.hip): output tiles of 64 x rows
 // nodes, rows in {8, 16, 24, 32} (32 not for FP64); nt: non-temporal stores
 int launch_step2(const Lattice& L, const void* src, void* dst, int rows, int nt);
+// four fused steps src -> dst (kbc_step4.hip): the launch shape that beats two
+// launches of two steps on this lattice with this store kind (0: none does),
+// and the launch
+int step4_shape(const Lattice& L, int nt);
+int launch_step4(const Lattice& L, const void* src, void* dst, int shape, int nt);
 int launch_init(const Lattice& L, void* dst, const double* rho, const double* ux, const double* uy,
                 const double* grad, int mode);
 int launch_moments(const Lattice& L, const void* src, double* rho, double* ux, double* uy,

@@ -18,38 +18,6 @@ namespace kbc {
 
 namespace {
 
-#ifndef KBC_PANEL
-#define KBC_PANEL 32
-#endif
-constexpr int kPanel = KBC_PANEL;   // tile columns per panel (a power of two)
-static_assert(kPanel > 0 && (kPanel & (kPanel - 1)) == 0, "panel width must be a power of two");
-
-// Tile (tx, ty) of panel-order index u: full panels of kPanel columns, then
-// one panel of the remaining `last` columns (0 if ntx is a multiple).
-// (With no full panel the order is row-major; otherwise kPanel * nty is at
-// most the tile count, which the host keeps below 2^24: a launch holds at
-// most 2^32 - 1 work-items.)
-__device__ __forceinline__ void panel_tile(int u, int ntx, int nty, int& tx, int& ty) {
-    const int full = ntx / kPanel;
-    if (full == 0) {
-        ty = u / ntx;
-        tx = u - ty * ntx;
-        return;
-    }
-    const int per_panel = kPanel * nty;
-    const int p = u / per_panel;
-    if (p < full) {
-        const int r = u - p * per_panel;
-        ty = r / kPanel;
-        tx = p * kPanel + (r & (kPanel - 1));
-    } else {
-        const int last = ntx - full * kPanel;
-        const int r = u - full * per_panel;
-        ty = r / last;
-        tx = full * kPanel + (r - ty * last);
-    }
-}
-
 template <int FORM, int COLL, int VAR, int GM, int TH, bool NT, bool SLAB>
 __global__ __launch_bounds__(256) void k_step2(const typename Form<FORM>::S* __restrict__ src,
                                                typename Form<FORM>::S* __restrict__ dst, int nx, int ny,

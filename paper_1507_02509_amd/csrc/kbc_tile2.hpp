@@ -53,6 +53,34 @@ __device__ __forceinline__ int wrap1(int v, int n) {
     return (v >= n) ? v - n : v;
 }
 
+constexpr int kPanel = 32;   // tile columns per panel (a power of two)
+
+// Tile (tx, ty) of panel-order index u (the launches' order of fused tiles): full panels of kPanel columns, then
+// one panel of the remaining `last` columns (0 if ntx is a multiple).
+// (With no full panel the order is row-major; otherwise kPanel * nty is at
+// most the tile count, which the host keeps below 2^24: a launch holds at
+// most 2^32 - 1 work-items.)
+__device__ __forceinline__ void panel_tile(int u, int ntx, int nty, int& tx, int& ty) {
+    const int full = ntx / kPanel;
+    if (full == 0) {
+        ty = u / ntx;
+        tx = u - ty * ntx;
+        return;
+    }
+    const int per_panel = kPanel * nty;
+    const int p = u / per_panel;
+    if (p < full) {
+        const int r = u - p * per_panel;
+        ty = r / kPanel;
+        tx = p * kPanel + (r & (kPanel - 1));
+    } else {
+        const int last = ntx - full * kPanel;
+        const int r = u - full * per_panel;
+        ty = r / last;
+        tx = full * kPanel + (r - ty * last);
+    }
+}
+
 // Two fused steps on the output tile with corner (x0, y0), for the 256
 // threads of the calling workgroup (all of which must call it: it holds a
 // workgroup barrier).  SLAB: the rows beyond the slab's edges, -2, -1 and
