@@ -107,7 +107,7 @@ __device__ __forceinline__ void collide_vjp(const R (&g)[9], const R (&mu)[9], c
         const bool active = n.active;
         R gam = n.gam;
         if constexpr (GM == GEXACT) {
-            if (active) gam = exact_gamma<R>(gam, ds, dh, w, ir, K);
+            if (active) gam = exact_gamma<R>(n, K);
         }
 
         // --------------------------------------------------------- reverse
