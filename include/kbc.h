@@ -226,10 +226,10 @@ int lbm_get_tile(const lbm_ctx* c, int32_t* width, int32_t* rows_per_thread, int
  * setting; the non-temporal flag of lbm_set_tile applies to the fused launch
  * too.  LBM_EINVAL for other values.  With 2 and the default height, calls of
  * eight steps or more may run groups of eight as two launches of four fused
- * steps: on lattices of at most one tile per CU, and where two steps per launch
- * are bound by memory (LBGK, a fixed stabiliser, FP32 beyond the last-level
- * cache); the state ends in the same buffer as without.  lbm_get_fusion returns
- * 1 or 2 as set and stores the fused tile height in *rows when rows is not NULL
+ * steps where that is faster (small lattices, and where two steps per launch
+ * are bound by memory); the state ends in the same buffer as without, and KBC
+ * writes it with non-temporal stores whatever the flag.  lbm_get_fusion
+ * returns 1 or 2 as set and stores the fused tile height in *rows when rows is not NULL
  * (-1 for a NULL ctx). */
 int lbm_set_fusion(lbm_ctx* c, int32_t steps_per_launch, int32_t rows);
 int lbm_get_fusion(const lbm_ctx* c, int32_t* rows);

@@ -26,6 +26,7 @@ struct lbm_ctx {
     int fuse;               // time steps per launch of lbm_step: 1 or 2
     int fuse_rows;          // output tile height of the fused launch: 8, 16, 24 or 32
     int default_rows;       // its default for this lattice
+    double state_bytes;     // of both population buffers
     double* dscratch;       // diagnostics: block partials (device)
     double* dresult;        // diagnostics: sums (pinned host memory the kernel writes)
     double* ascratch;       // adjoint: block partials + initial-state stencil fields
@@ -183,7 +184,8 @@ int lbm_init(lbm_ctx** out, const lbm_params* p, void* buf_a, void* buf_b, size_
     c->cur = 0;
     c->steps = 0;
     c->shape = default_shape(p->form);
-    if (plain_stores_pay(p->form, 2.0 * static_cast<double>(bytes))) c->shape.nt = 0;
+    c->state_bytes = 2.0 * static_cast<double>(bytes);
+    if (plain_stores_pay(p->form, c->state_bytes)) c->shape.nt = 0;
     // two fused steps per launch by default for every form (measured for
     // KBC-B at 16384^2: FP32 +38 %, FP64 +25 %, FP16 +6 % over single steps;
     // the ring of extra step-1 collisions costs less than the HBM pass it saves)
@@ -231,12 +233,13 @@ int step_eager(lbm_ctx* c, int32_t nsteps) {
     // another fused tile.  An even number of such launches: each takes the
     // place of two launches of two steps, so the state ends in the same buffer
     // as without them (an ensemble's members must agree on it).
+    const int32_t size[2] = {c->p.nx, c->p.ny};
     const int shape4 = (c->fuse == 2 && c->fuse_rows == c->default_rows && nsteps >= 8)
-                           ? kbc::step4_shape(c->L, c->shape.nt) : 0;
+                           ? kbc::step4_shape(c->L, size, 1, c->state_bytes, c->shape.nt, true) : 0;
     if (shape4) {
         for (; s + 8 <= nsteps; s += 8)
             for (int k = 0; k < 2; ++k) {
-                const int rc = kbc::launch_step4(c->L, c->buf[c->cur], c->buf[c->cur ^ 1], shape4, c->shape.nt);
+                const int rc = kbc::launch_step4(c->L, c->buf[c->cur], c->buf[c->cur ^ 1], shape4);
                 if (rc) return launch_result(rc, "lbm_step (four fused steps)");
                 c->cur ^= 1;
                 c->steps += 4;

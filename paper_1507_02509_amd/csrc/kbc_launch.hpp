@@ -53,11 +53,16 @@ int launch_step(const Lattice& L, const void* src, void* dst, const StepShape& s
 // two fused steps src -> dst (kbc_step2.hip): output tiles of 64 x rows
 // nodes, rows in {8, 16, 24, 32} (32 not for FP64); nt: non-temporal stores
 int launch_step2(const Lattice& L, const void* src, void* dst, int rows, int nt);
-// four fused steps src -> dst (kbc_step4.hip): the launch shape that beats two
-// launches of two steps on this lattice with this store kind (0: none does),
-// and the launch
-int step4_shape(const Lattice& L, int nt);
-int launch_step4(const Lattice& L, const void* src, void* dst, int shape, int nt);
+// four fused steps src -> dst (kbc_step4.hip): the code of the launch shape
+// that beats two launches of two steps (0: none does) on `count` lattices of
+// sizes (nx, ny), (nx, ny), ... stepped together, whose buffers hold
+// state_bytes, with this store kind (one_per_cu: the launch has the shapes of
+// at most one tile per CU); rows and waves per workgroup of a code; and the
+// launch
+int step4_shape(const Lattice& L, const int32_t* sizes, int count, double state_bytes, int nt, bool one_per_cu);
+inline int step4_rows(int code) { return code & 0xff; }
+inline int step4_waves(int code) { return code >> 8 & 0xff; }
+int launch_step4(const Lattice& L, const void* src, void* dst, int shape);
 int launch_init(const Lattice& L, void* dst, const double* rho, const double* ux, const double* uy,
                 const double* grad, int mode);
 int launch_moments(const Lattice& L, const void* src, double* rho, double* ux, double* uy,
@@ -131,6 +136,9 @@ int64_t adjoint_slice_len(const Lattice& L);
 int launch_sum_slices(const double* slices, int64_t len, int k, double* tot, double* acc, hipStream_t stream);
 int launch_adjoint_seed(const Lattice& L, const void* state, const double* drho, const double* dux,
                         const double* duy, void* lam);
+// four fused steps per launch (kbc_ensemble4.hip, never persistent); a.rows is a step4_shape code,
+// the table's tiles are 64 x step4_rows(a.rows)
+int launch_ensemble4(const Lattice& L, const EnsLaunch& a);
 // fsrc / fdst (both or neither): one forward step between two other state
 // buffers, run in the same launch as the adjoint step
 int launch_adjoint_step(const Lattice& L, const void* state, const void* lin, void* lout, double* partials,

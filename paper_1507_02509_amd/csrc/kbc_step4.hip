@@ -1,29 +1,29 @@
 // kbc_step4.hip -- four fused time steps per launch on a single lattice; the
 // tile body is stepn_tile (kbc_tilen.hpp).
 //
-// Where four steps pay against two (step4_shape):
+// Where four steps pay against two (step4_shape), us per step with two / four
+// steps per launch:
 //
 //   * Small lattices, at most one tile per CU.  There a launch is a chain of
 //     latencies (about 2.4 us for the launch itself, then the loads, then one
 //     collision after another), and the arithmetic repeated in the tiles'
 //     margins costs nothing while CUs are idle.  The smallest tile height that
 //     still gives every CU at most one tile is taken, with enough waves that
-//     each has one row or two per step.  us per step, two / four steps per
-//     launch: FP32 KBC-B 64^2 2.55 / 1.27, 256^2 2.74 / 1.51, 320^2 2.86 / 1.85,
-//     384^2 3.48 / 2.23, 512^2 3.64 / 2.67, 640^2 4.60 / 4.12; FP64 64^2 3.14 /
-//     1.70, 512^2 5.31 / 4.44; FP16 512^2 3.80 / 3.03; exact stabiliser FP32
-//     512^2 9.03 / 6.94.
-//   * Lattices bound by memory at two steps per launch: LBGK and the fixed
-//     stabiliser in every form, and FP32 KBC beyond the last-level cache.  Four
-//     steps halve the traffic for a quarter more collisions in the margins.
-//     FP32 LBGK 4096^2 118 / 71.5 us, 1024^2 (plain stores) 7.15 / 5.57; FP64
-//     LBGK 2048^2 58.5 / 43.0; FP16 LBGK 3072^2 46.0 / 40.4; FP32 KBC-B
-//     4096^2 123 / 109.5.
+//     each has one row or two per step.  FP32 KBC-B 64^2 2.55 / 1.27, 256^2 2.74 /
+//     1.51, 320^2 2.86 / 1.85, 384^2 3.48 / 2.23, 512^2 3.64 / 2.67, 640^2 4.60 /
+//     4.12; FP64 64^2 3.14 / 1.70, 512^2 5.31 / 4.44; FP16 512^2 3.80 / 3.03;
+//     FP32 LBGK 512^2 2.86 / 1.86; exact stabiliser FP32 512^2 9.03 / 6.94.
+//   * Larger ones that memory binds at two steps: LBGK and the fixed
+//     stabiliser in every form, FP32 and FP64 KBC, FP16 KBC beyond the
+//     last-level cache.  Four steps halve the traffic for a quarter more
+//     collisions in the margins.  FP32 LBGK 4096^2 117 / 68, FP64 LBGK 2048^2
+//     58.2 / 37.3, FP16 LBGK 3072^2 44.6 / 38.0; FP32 KBC-B 8192^2 477 / 391,
+//     4096^2 122 / 98, 1280^2 13.8 / 12.4, 1024^2 9.1 / 9.1; FP64 KBC-B 3072^2 138 /
+//     127, 1024^2 15.7 / 15.7; FP16 KBC-B 4096^2 106 / 99.
 //
-// Two steps stay where arithmetic binds: FP16 and FP64 KBC and the exact
-// stabiliser beyond one tile per CU (FP16 KBC-B 3072^2 61.1 / 67.9 us, FP64
-// 138 / 140, exact 150 / 168), and FP32 KBC inside the last-level cache (1536^2
-// 17.5 / 17.7).
+// Two steps stay where arithmetic binds: FP16 KBC inside the last-level cache
+// (1536^2 17.4 / 17.9) and the exact stabiliser beyond one tile per CU (1024^2
+// 15.0 / 16.7).
 #include "kbc_launch.hpp"
 #include "kbc_tilen.hpp"
 
@@ -31,13 +31,13 @@ namespace kbc {
 
 namespace {
 
-// at most one tile per CU: 256 CUs
 constexpr int64_t kCus = 256;
-// Shapes of many tiles per CU are numbered apart from the heights of one
-constexpr int kManyTiles = 64;
 
-int64_t tiles_of(const Lattice& L, int rows) {
-    return static_cast<int64_t>((L.nx + 63) / 64) * ((L.ny + rows - 1) / rows);
+// Wave tasks of one tile: its rows and packed margin nodes over four steps.
+constexpr int tasks_of(int rows) {
+    int n = rows;
+    for (int h = 1; h <= 3; ++h) n += rows + 2 * h + (2 * h * (rows + 2 * h) + 63) / 64;
+    return n;
 }
 
 template <int FORM, int COLL, int VAR, int GM, int TH, int NW, bool NT>
@@ -70,59 +70,76 @@ struct Step4Op {
             make_coef<typename F::R>(L));
         return hipGetLastError() == hipSuccess ? 0 : -2;
     }
-    static int run(const Lattice& L, const void* src, void* dst, int shape, int nt) {
-        constexpr bool kWide = FORM == F64;   // FP64: taller windows leave room for fewer waves' registers
-        constexpr bool kLight = COLL == LBGK || GM == GFIX;
-        switch (shape) {
-            case 2: return go<2, 10, true>(L, src, dst);
-            case 4: return go<4, 12, true>(L, src, dst);
-            case 8: return go<8, 16, true>(L, src, dst);
-            case 12: return go<12, kWide ? 12 : 16, true>(L, src, dst);
-            case 16: return go<16, kWide ? 12 : 16, true>(L, src, dst);
-            case 28:
-                if constexpr (FORM != F64) return go<28, 12, true>(L, src, dst);
-                return -1;
-            case kManyTiles + 12:
-                if constexpr (kLight && FORM == F64)
-                    return nt ? go<12, 8, true>(L, src, dst) : go<12, 8, false>(L, src, dst);
-                if constexpr (kLight && FORM == F32) return go<12, 8, false>(L, src, dst);
-                return -1;
-            case kManyTiles + 24:
-                if constexpr (FORM == F32 && kLight) return go<24, 12, true>(L, src, dst);
-                if constexpr (FORM == F32 && COLL == KBCC && GM == GEST) return go<24, 8, true>(L, src, dst);
-                if constexpr (FORM == F16 && kLight)
-                    return nt ? go<24, 8, true>(L, src, dst) : go<24, 8, false>(L, src, dst);
-                return -1;
-            default: return -1;
+    // called by step4_one / step4_many for the launch's shape
+    struct Launch {
+        const Lattice& L;
+        const void* src;
+        void* dst;
+        template <int TH, int NW, bool NT>
+        int at() const {
+            return go<TH, NW, NT>(L, src, dst);
         }
+    };
+    static int run(const Lattice& L, const void* src, void* dst, int sh) {
+        const int rc = step4_one<FORM, COLL, VAR, GM>(sh, Launch{L, src, dst});
+        return rc == -1 ? step4_many<FORM, COLL, VAR, GM>(sh, Launch{L, src, dst}) : rc;
     }
 };
 
 }  // namespace
 
-int step4_shape(const Lattice& L, int nt) {
+int step4_shape(const Lattice& L, const int32_t* sizes, int count, double state_bytes, int nt, bool one_per_cu) {
     if (L.halo_lo) return 0;   // a slab's halo holds the rows for two steps
-    // small lattices (their default store kind is non-temporal: the other,
-    // set by the caller, keeps two steps)
-    if (nt) {
-        for (int rows : {2, 4, 8, 12, 16, 28})
-            if (tiles_of(L, rows) <= kCus && (rows != 28 || L.form != F64) && (rows != 2 || tiles_of(L, 2) <= kCus / 2))
-                return rows;
+    auto tiles = [&](int rows) {
+        int64_t n = 0;
+        for (int k = 0; k < count; ++k)
+            n += static_cast<int64_t>((sizes[2 * k] + 63) / 64) * ((sizes[2 * k + 1] + rows - 1) / rows);
+        return n;
+    };
+    auto shape = [](int rows, int waves, bool store_nt = true) { return step4_code(rows, waves, store_nt); };
+    // one tile per CU (an ensemble's launches are built for many).  Two rows only up to half of that: a tile's six margin
+    // rows weigh most there (192^2 with 288 such tiles 1.82, with four rows
+    // 1.44).  FP64 has room for fewer waves' registers, and not for 28 rows.
+    const bool f64 = L.form == F64;
+    if (one_per_cu) {
+        if (tiles(2) <= kCus / 2) return shape(2, 10);
+        if (tiles(4) <= kCus) return shape(4, 12);
+        if (tiles(8) <= kCus) return shape(8, 16);
+        if (tiles(12) <= kCus) return shape(12, f64 ? 12 : 16);
+        if (tiles(16) <= kCus) return shape(16, f64 ? 12 : 16);
+        if (!f64 && tiles(28) <= kCus) return shape(28, 12);
+    } else if (tiles(16) <= kCus) {
+        return 0;
     }
+    // many tiles per CU.  Plain stores matter to the light collisions only,
+    // which the last-level cache feeds (FP32 LBGK 1280^2: plain 7.1, others
+    // 8.6); KBC measures the same or 1 % better with non-temporal ones.
+    if (L.collision != LBGK && L.gamma_mode == GEXACT) return 0;
     const bool light = L.collision == LBGK || L.gamma_mode == GFIX;
-    if (light) {
-        if (L.form == F64) return kManyTiles + 12;
-        if (L.form == F16) return kManyTiles + 24;
-        return kManyTiles + (nt ? 24 : 12);
+    if (f64) return L.collision == LBGK ? shape(12, 12, nt != 0) : shape(12, 8, !light || nt != 0);
+    if (L.form == F16) {
+        if (light) return shape(24, 8, nt != 0);
+        return state_bytes > 256.0 * 1024.0 * 1024.0 ? shape(32, 8) : 0;
     }
-    // FP32 KBC: where both state buffers outgrow the 256 MiB last-level cache
-    const double state_bytes = 2.0 * 9.0 * 4.0 * static_cast<double>(L.pitch) * L.ny;
-    if (L.form == F32 && L.gamma_mode == GEST && nt && state_bytes > 256.0 * 1024.0 * 1024.0) return kManyTiles + 24;
-    return 0;
+    if (light && !nt) return shape(12, 8, false);
+    // FP32: the height whose busiest CU has the least to do.  The order this
+    // gives is the measured one on 1200^2, 900 x 1500, 800^2, 1024^2, 1536^2,
+    // 1921 x 1083, 2600 x 700, 640 x 1500, 2048^2 and 4096^2 (1200^2: 24, 16, 20,
+    // 28 rows 11.6, 11.8, 12.0, 12.1)
+    int best_rows = 0;
+    int64_t best_cost = 0;
+    for (int rows : {28, 24, 20, 16, 12}) {
+        const int64_t cost = ((tiles(rows) + kCus - 1) / kCus) * tasks_of(rows);
+        if (!best_rows || cost < best_cost) {
+            best_cost = cost;
+            best_rows = rows;
+        }
+    }
+    return best_rows == 28 ? shape(28, 12) : shape(best_rows, 8);
 }
 
-int launch_step4(const Lattice& L, const void* src, void* dst, int shape, int nt) {
-    return dispatch<Step4Op>(L, src, dst, shape, nt);
+int launch_step4(const Lattice& L, const void* src, void* dst, int shape) {
+    return dispatch<Step4Op>(L, src, dst, shape);
 }
 
 }  // namespace kbc

@@ -58,9 +58,9 @@ __device__ __forceinline__ void stepn_rest(typename Form<FORM>::S* __restrict__ 
     const int rows = th + 2 * H, side = 2 * H * rows;
     constexpr bool even = S % 2 == 0;
     __syncthreads();
-    // the node at window row r, column c
-    auto node = [&](int r, int c, R (&g)[9]) {
-        const E* p = win + r * WW + c;
+    // the node at window offset o (row * WW + column)
+    auto node = [&](int o, R (&g)[9]) {
+        const E* p = win + o;
 #pragma unroll
         for (int i = 0; i < 9; ++i) {
             if constexpr (even)
@@ -70,39 +70,33 @@ __device__ __forceinline__ void stepn_rest(typename Form<FORM>::S* __restrict__ 
         }
         collide<R, COLL, VAR, GM>(g, K);
     };
-    auto leave = [&](int r, int c, const R (&g)[9]) {
-        E* p = win + r * WW + c;
-#pragma unroll
-        for (int i = 0; i < 9; ++i) {
-            if constexpr (even)
-                p[opp(i) * WH * WW] = F::enc(g[i], i);
-            else
-                p[i * WH * WW + kCy[i] * WW + kCx[i]] = F::enc(g[i], i);
-        }
-    };
     for (int t = w; t < packed + rows; t += NW) {
         R g[9];
-        if (t < packed) {
-            const int k = t * 64 + lane;
-            if (k < side) {
-                const int r = k / (H > 0 ? 2 * H : 1), q = k - r * 2 * H;
-                const int c = q < H ? q : q + 64;
-                node(r + M - H, c + M - H, g);
-                leave(r + M - H, c + M - H, g);
+        if constexpr (S < T) {
+            int o = (t - packed + M - H) * WW + lane + M;
+            bool on = true;
+            if (t < packed) {
+                const int k = t * 64 + lane;
+                const int r = k / (2 * H), q = k - r * 2 * H;
+                o = (r + M - H) * WW + (q < H ? q : q + 64) + M - H;
+                on = k < side;
             }
-        } else {
-            const int r = t - packed;
-            if constexpr (S < T) {
-                node(r + M - H, lane + M, g);
-                leave(r + M - H, lane + M, g);
-            } else {
-                if (x0 + lane < nx) {
-                    node(r + M, lane + M, g);
-                    const uint32_t c0 = static_cast<uint32_t>(x0 + lane) * sizeof(E);
+            if (on) {
+                node(o, g);
+                E* p = win + o;
 #pragma unroll
-                    for (int i = 0; i < 9; ++i) st_at<NT>(row_ptr(dst, y0 + r, i, pitch), c0, F::enc(g[i], i));
+                for (int i = 0; i < 9; ++i) {
+                    if constexpr (even)
+                        p[opp(i) * WH * WW] = F::enc(g[i], i);
+                    else
+                        p[i * WH * WW + kCy[i] * WW + kCx[i]] = F::enc(g[i], i);
                 }
             }
+        } else if (x0 + lane < nx) {
+            node((t + M) * WW + lane + M, g);
+            const uint32_t c0 = static_cast<uint32_t>(x0 + lane) * sizeof(E);
+#pragma unroll
+            for (int i = 0; i < 9; ++i) st_at<NT>(row_ptr(dst, y0 + t, i, pitch), c0, F::enc(g[i], i));
         }
     }
     if constexpr (S < T)
@@ -132,63 +126,137 @@ __device__ __forceinline__ void stepn_tile(const typename Form<FORM>::S* __restr
     const uint32_t c0 = static_cast<uint32_t>(gx) * sizeof(E);
     const uint32_t cm = static_cast<uint32_t>(gx == 0 ? nx - 1 : gx - 1) * sizeof(E);
     const uint32_t cp = static_cast<uint32_t>(gx == nx - 1 ? 0 : gx + 1) * sizeof(E);
-    for (int t = w; t < packed + rows; t += NW) {
+    auto load_row = [&](int r, E (&v)[9]) {
+        const int y = wrap_uniform(y0 + r - H, ny), ym = y == 0 ? ny - 1 : y - 1, yp = y == ny - 1 ? 0 : y + 1;
+        v[0] = ld_at(row_ptr(src, y, 0, pitch), c0);
+        v[1] = ld_at(row_ptr(src, y, 1, pitch), cm);
+        v[2] = ld_at(row_ptr(src, ym, 2, pitch), c0);
+        v[3] = ld_at(row_ptr(src, y, 3, pitch), cp);
+        v[4] = ld_at(row_ptr(src, yp, 4, pitch), c0);
+        v[5] = ld_at(row_ptr(src, ym, 5, pitch), cm);
+        v[6] = ld_at(row_ptr(src, ym, 6, pitch), cp);
+        v[7] = ld_at(row_ptr(src, yp, 7, pitch), cp);
+        v[8] = ld_at(row_ptr(src, yp, 8, pitch), cm);
+    };
+    auto row = [&](int r, const E (&v)[9]) {
         R g[9];
-        if (t < packed) {
-            const int k = t * 64 + lane;
-            if (k < side) {
-                const int r = k / (2 * H), q = k - r * 2 * H;
-                const int c = q < H ? q : q + 64;              // extended column, 0 .. 64 + 2 H - 1
-                const int x = pmod(x0 + c - H, nx), y = pmod(y0 + r - H, ny);
-                const int xm = wrap1(x - 1, nx), xp = wrap1(x + 1, nx);
-                const E* p0 = src + static_cast<int64_t>(y) * 9 * pitch;
-                const E* pm = src + static_cast<int64_t>(wrap1(y - 1, ny)) * 9 * pitch;
-                const E* pp = src + static_cast<int64_t>(wrap1(y + 1, ny)) * 9 * pitch;
-                E v[9];
-                v[0] = p0[x];
-                v[1] = p0[pitch + xm];
-                v[2] = pm[2 * pitch + x];
-                v[3] = p0[3 * pitch + xp];
-                v[4] = pp[4 * pitch + x];
-                v[5] = pm[5 * pitch + xm];
-                v[6] = pm[6 * pitch + xp];
-                v[7] = pp[7 * pitch + xp];
-                v[8] = pp[8 * pitch + xm];
 #pragma unroll
-                for (int i = 0; i < 9; ++i) g[i] = F::dec(v[i], i);
-                collide<R, COLL, VAR, GM>(g, K);
-                // window column c - 1 (+ v_x), window row r - 1 (+ v_y): the
-                // outer ring's outward populations have no slot
+        for (int i = 0; i < 9; ++i) g[i] = F::dec(v[i], i);
+        collide<R, COLL, VAR, GM>(g, K);
 #pragma unroll
-                for (int i = 0; i < 9; ++i) {
-                    const int a = r - 1 + kCy[i], b = c - 1 + kCx[i];
-                    if (a >= 0 && a < WH && b >= 0 && b < WW) win[(i * WH + a) * WW + b] = F::enc(g[i], i);
-                }
-            }
-        } else {
-            const int r = t - packed;
-            const int y = wrap_uniform(y0 + r - H, ny), ym = y == 0 ? ny - 1 : y - 1, yp = y == ny - 1 ? 0 : y + 1;
-            E v[9];
-            v[0] = ld_at(row_ptr(src, y, 0, pitch), c0);
-            v[1] = ld_at(row_ptr(src, y, 1, pitch), cm);
-            v[2] = ld_at(row_ptr(src, ym, 2, pitch), c0);
-            v[3] = ld_at(row_ptr(src, y, 3, pitch), cp);
-            v[4] = ld_at(row_ptr(src, yp, 4, pitch), c0);
-            v[5] = ld_at(row_ptr(src, ym, 5, pitch), cm);
-            v[6] = ld_at(row_ptr(src, ym, 6, pitch), cp);
-            v[7] = ld_at(row_ptr(src, yp, 7, pitch), cp);
-            v[8] = ld_at(row_ptr(src, yp, 8, pitch), cm);
+        for (int i = 0; i < 9; ++i) {
+            const int a = r - 1 + kCy[i];
+            if (a >= 0 && a < WH) win[(i * WH + a) * WW + lane + M + kCx[i]] = F::enc(g[i], i);
+        }
+    };
+    // the wave's rows: the first one's loads are in flight during the packed
+    // nodes, the next one's while a row collides (two register sets, as in
+    // step2_tile)
+    int r = (w - packed % NW + NW) % NW;
+    E va[9], vb[9];
+    if (r < rows) load_row(r, va);
+    for (int t = w; t < packed; t += NW) {
+        const int k = t * 64 + lane;
+        if (k >= side) continue;
+        const int q = k / (2 * H), m = k - q * 2 * H;
+        const int c = m < H ? m : m + 64;                  // extended column, 0 .. 64 + 2 H - 1
+        const int x = pmod(x0 + c - H, nx), y = pmod(y0 + q - H, ny);
+        const int xm = wrap1(x - 1, nx), xp = wrap1(x + 1, nx);
+        const E* p0 = src + static_cast<int64_t>(y) * 9 * pitch;
+        const E* pm = src + static_cast<int64_t>(wrap1(y - 1, ny)) * 9 * pitch;
+        const E* pp = src + static_cast<int64_t>(wrap1(y + 1, ny)) * 9 * pitch;
+        E v[9];
+        v[0] = p0[x];
+        v[1] = p0[pitch + xm];
+        v[2] = pm[2 * pitch + x];
+        v[3] = p0[3 * pitch + xp];
+        v[4] = pp[4 * pitch + x];
+        v[5] = pm[5 * pitch + xm];
+        v[6] = pm[6 * pitch + xp];
+        v[7] = pp[7 * pitch + xp];
+        v[8] = pp[8 * pitch + xm];
+        R g[9];
 #pragma unroll
-            for (int i = 0; i < 9; ++i) g[i] = F::dec(v[i], i);
-            collide<R, COLL, VAR, GM>(g, K);
+        for (int i = 0; i < 9; ++i) g[i] = F::dec(v[i], i);
+        collide<R, COLL, VAR, GM>(g, K);
+        // window column c - 1 (+ v_x), window row q - 1 (+ v_y): the outer
+        // ring's outward populations have no slot
 #pragma unroll
-            for (int i = 0; i < 9; ++i) {
-                const int a = r - 1 + kCy[i];
-                if (a >= 0 && a < WH) win[(i * WH + a) * WW + lane + M + kCx[i]] = F::enc(g[i], i);
-            }
+        for (int i = 0; i < 9; ++i) {
+            const int a = q - 1 + kCy[i], b = c - 1 + kCx[i];
+            if (a >= 0 && a < WH && b >= 0 && b < WW) win[(i * WH + a) * WW + b] = F::enc(g[i], i);
         }
     }
+    for (; r + 2 * NW < rows; r += 2 * NW) {
+        load_row(r + NW, vb);
+        row(r, va);
+        load_row(r + 2 * NW, va);
+        row(r + NW, vb);
+    }
+    if (r + NW < rows) {
+        load_row(r + NW, vb);
+        row(r, va);
+        row(r + NW, vb);
+    } else if (r < rows) {
+        row(r, va);
+    }
     stepn_rest<FORM, COLL, VAR, GM, T, TH, NW, NT, 2>(win, dst, nx, ny, pitch, x0, y0, th, lane, w, K);
+}
+
+// Launch shapes of four steps: tile rows, waves per workgroup and store kind
+// as one code, and the call of a launcher's at<TH, NW, NT>() for a code.
+constexpr int step4_code(int rows, int waves, bool nt = true) { return rows | waves << 8 | (nt ? 1 << 16 : 0); }
+
+// The shapes of many tiles per CU: the ones step4_shape (kbc_step4.hip)
+// chooses for a collision.
+template <int FORM, int COLL, int VAR, int GM, typename Launch>
+int step4_many(int code, const Launch& l) {
+    constexpr bool kFix = COLL == KBCC && GM == GFIX, kEst = COLL == KBCC && GM == GEST;
+    constexpr bool kLight = COLL == LBGK || kFix;
+    if constexpr (FORM == F32 && (kLight || kEst)) {
+        switch (code) {
+            case step4_code(12, 8): return l.template at<12, 8, true>();
+            case step4_code(16, 8): return l.template at<16, 8, true>();
+            case step4_code(20, 8): return l.template at<20, 8, true>();
+            case step4_code(24, 8): return l.template at<24, 8, true>();
+            case step4_code(28, 12): return l.template at<28, 12, true>();
+            default: break;
+        }
+    }
+    if constexpr (FORM == F32 && kLight)
+        if (code == step4_code(12, 8, false)) return l.template at<12, 8, false>();
+    if constexpr (FORM == F16 && kLight) {
+        if (code == step4_code(24, 8)) return l.template at<24, 8, true>();
+        if (code == step4_code(24, 8, false)) return l.template at<24, 8, false>();
+    }
+    if constexpr (FORM == F16 && kEst)
+        if (code == step4_code(32, 8)) return l.template at<32, 8, true>();
+    if constexpr (FORM == F64 && COLL == LBGK) {
+        if (code == step4_code(12, 12)) return l.template at<12, 12, true>();
+        if (code == step4_code(12, 12, false)) return l.template at<12, 12, false>();
+    }
+    if constexpr (FORM == F64 && (kFix || kEst))
+        if (code == step4_code(12, 8)) return l.template at<12, 8, true>();
+    if constexpr (FORM == F64 && kFix)
+        if (code == step4_code(12, 8, false)) return l.template at<12, 8, false>();
+    return -1;
+}
+
+// The shapes of at most one tile per CU, for every collision.
+template <int FORM, int COLL, int VAR, int GM, typename Launch>
+int step4_one(int code, const Launch& l) {
+    constexpr int w = FORM == F64 ? 12 : 16;
+    switch (code) {
+        case step4_code(2, 10): return l.template at<2, 10, true>();
+        case step4_code(4, 12): return l.template at<4, 12, true>();
+        case step4_code(8, 16): return l.template at<8, 16, true>();
+        case step4_code(12, w): return l.template at<12, w, true>();
+        case step4_code(16, w): return l.template at<16, w, true>();
+        default: break;
+    }
+    if constexpr (FORM != F64)
+        if (code == step4_code(28, 12)) return l.template at<28, 12, true>();
+    return -1;
 }
 
 }  // namespace kbc
