@@ -819,6 +819,13 @@ int64_t ens_table(const lbm_ens* e, int tw, int th, std::vector<kbc::EnsEntry>& 
         t.buf[0] = c->buf[0];
         t.buf[1] = c->buf[1];
         t.nx = c->p.nx;
+    int default_rows;           // fused tile height the library chose
+    double state_bytes;         // of all members' buffers
+    int shape4;                 // launch shape of four fused steps (0: pairs are as fast)
+    kbc::EnsEntry* dtab4;       // member table, tile count and tile index for it
+    int ntiles4;
+    int32_t* dmap4;
+    int64_t dmap4_len;
         t.ny = c->p.ny;
         t.ntx = (c->p.nx + tw - 1) / tw;
         t.pitch = c->L.pitch;
@@ -909,6 +916,25 @@ int lbm_set_halo(lbm_ctx* c, const void* lo, const void* hi) {
     int rc = graph_reset(c);
     if (rc) return rc;
     if (lo) c->graph_chunk = 0;
+    std::vector<int32_t> sizes;
+    for (const lbm_ctx* c : e->m) {
+        sizes.push_back(c->p.nx);
+        sizes.push_back(c->p.ny);
+    }
+    e->shape4 = kbc::step4_shape(e->L, sizes.data(), static_cast<int>(e->m.size()), e->state_bytes, e->shape.nt,
+                                 false);
+    if (e->shape4) {
+        const int64_t tiles4 = ens_table(e, 64, kbc::step4_rows(e->shape4), tab);
+        if (tiles4 < 0 || !kbc::grid_fits(8 * ((tiles4 + 7) / 8), 64 * kbc::step4_waves(e->shape4))) {
+            e->shape4 = 0;
+        } else {
+            rc = ens_upload(e, &e->dtab4, tab);
+            if (rc) return rc;
+            rc = ens_map(e, tab, tiles4, &e->dmap4, &e->dmap4_len);
+            if (rc) return rc;
+            e->ntiles4 = static_cast<int>(tiles4);
+        }
+    }
     c->L.halo_lo = lo;
     c->L.halo_hi = hi;
     return LBM_OK;
@@ -969,7 +995,7 @@ int lbm_ensemble_create(lbm_ens** out, lbm_ctx* const* members, int32_t count) {
     e->spin_limit = LBM_ENSEMBLE_SPIN_DEFAULT;
     // two fused steps per launch, as for single lattices
     e->fuse = 2;
-    e->rows = (m0->p.form == LBM_F64) ? 8 : 16;
+    e->rows = e->default_rows = (m0->p.form == LBM_F64) ? 8 : 16;
     int rc = ens_build(e);
     if (!rc) {
         hipError_t err = hipMalloc(&e->dsync, sizeof(kbc::EnsSync));
@@ -980,7 +1006,13 @@ int lbm_ensemble_create(lbm_ens** out, lbm_ctx* const* members, int32_t count) {
         if (e->dsync) (void)hipFree(e->dsync);
         if (e->dtab) (void)hipFree(e->dtab);
         if (e->dtab2) (void)hipFree(e->dtab2);
+        e->state_bytes = state;
         if (e->dmap2) (void)hipFree(e->dmap2);
+    e->shape4 = 0;
+    e->dtab4 = nullptr;
+    e->ntiles4 = 0;
+    e->dmap4 = nullptr;
+    e->dmap4_len = 0;
         if (e->dmap) (void)hipFree(e->dmap);
         delete e;
         return rc;
@@ -1004,6 +1036,8 @@ int lbm_ensemble_set_tile(lbm_ens* e, int32_t width, int32_t rows_per_thread, in
 
 int lbm_ensemble_blocks(const lbm_ens* e) {
     if (!e) return fail(LBM_EINVAL, "ensemble is NULL");
+        if (e->dtab4) (void)hipFree(e->dtab4);
+        if (e->dmap4) (void)hipFree(e->dmap4);
     int blocks = 0;
     kbc::EnsLaunch a{};
     a.shape = e->shape;
@@ -1055,8 +1089,11 @@ int lbm_ensemble_step(lbm_ens* e, int32_t nsteps, int32_t persistent) {
     const int cur = e->m[0]->cur;
     for (size_t r = 1; r < e->m.size(); ++r)
         if (e->m[r]->cur != cur) return fail(LBM_EINVAL, "members hold their states in different buffers");
-    const int pairs = (e->fuse == 2) ? nsteps / 2 : 0;
-    const int singles = nsteps - 2 * pairs;
+    // four steps per launch as in lbm_step: an even number of such launches,
+    // so that the members' states end in the same buffers as without them
+    const int fours = (e->fuse == 2 && e->rows == e->default_rows && e->shape4 && !persistent) ? nsteps / 8 * 2 : 0;
+    const int pairs = (e->fuse == 2) ? (nsteps - 4 * fours) / 2 : 0;
+    const int singles = nsteps - 4 * fours - 2 * pairs;
     kbc::EnsLaunch a{};
     a.nmem = static_cast<int>(e->m.size());
     a.sync = e->dsync;
@@ -1087,6 +1124,17 @@ int lbm_ensemble_step(lbm_ens* e, int32_t nsteps, int32_t persistent) {
         const int rc = kbc::launch_ensemble(e->L, a);
         if (rc) return launch_result(rc, "lbm_ensemble_step");
         par ^= (singles & 1);
+    if (fours) {
+        a.table = e->dtab4;
+        a.tile_member = e->dmap4;
+        a.ntiles = e->ntiles4;
+        a.nsteps = fours;
+        a.parity = par;
+        a.rows = e->shape4;
+        const int rc = kbc::launch_ensemble4(e->L, a);
+        if (rc) return launch_result(rc, "lbm_ensemble_step (four fused steps)");
+        a.rows = e->rows;
+    }
     }
     for (lbm_ctx* c : e->m) {
         c->cur = par;
@@ -1137,3 +1185,5 @@ int lbm_copy_probe(void* dst, const void* src, size_t n_words, void* stream) {
 }
 
 }  // extern "C"
+        if (e->dtab4) (void)hipFree(e->dtab4);
+        if (e->dmap4) (void)hipFree(e->dmap4);

@@ -14,6 +14,7 @@
 //     single-lattice step, kbc_tile.hpp);
 //   * k_ens2: one launch per two fused steps, one workgroup per 64 x TH output
 //     tile (tile body of the single-lattice fused kernel, kbc_tile2.hpp);
+//   * k_ens4 (kbc_ensemble4.hip): one launch per four fused steps;
 //   * k_ens_persist / k_ens2_persist: ONE launch for many steps (or pairs of
 //     steps): as many workgroups as the GPU holds at once, each taking tiles
 //     of its XCD's band as it asks for them (BandTiles), with a grid barrier
@@ -40,18 +41,6 @@
 namespace kbc {
 
 namespace {
-
-template <typename R>
-__device__ __forceinline__ Coef<R> coef_of(const EnsEntry& e) {
-    Coef<R> K;
-    K.beta = static_cast<R>(e.beta);
-    K.inv_beta = static_cast<R>(e.inv_beta);
-    K.two_m_inv_beta = static_cast<R>(e.two_m_inv_beta);
-    K.rho0 = static_cast<R>(e.rho0);
-    K.guard = static_cast<R>(e.guard);
-    K.gamma_fixed = static_cast<R>(e.gamma_fixed);
-    return K;
-}
 
 // Barrier number `b` (1, 2, ...) over the whole grid of a persistent launch.
 // Arrival is counted in two levels so that no single counter takes every

@@ -89,6 +89,19 @@ struct EnsEntry {
     int64_t pitch;
     double beta, inv_beta, two_m_inv_beta, rho0, guard, gamma_fixed;
 };
+// coefficients of a table entry
+template <typename R>
+__device__ __forceinline__ Coef<R> coef_of(const EnsEntry& e) {
+    Coef<R> K;
+    K.beta = static_cast<R>(e.beta);
+    K.inv_beta = static_cast<R>(e.inv_beta);
+    K.two_m_inv_beta = static_cast<R>(e.two_m_inv_beta);
+    K.rho0 = static_cast<R>(e.rho0);
+    K.guard = static_cast<R>(e.guard);
+    K.gamma_fixed = static_cast<R>(e.gamma_fixed);
+    return K;
+}
+
 // Grid-barrier state of a persistent ensemble launch (device memory owned by
 // the ensemble): eight group arrival counters (one per XCD band of
 // workgroups), the count of groups that have arrived, this launch's give-up
@@ -123,6 +136,9 @@ int launch_ensemble(const Lattice& L, const EnsLaunch& a);
 // two fused steps per launch for every member; a.nsteps counts launches, the
 // table's tiles are 64 x a.rows (kbc_ensemble.hip)
 int launch_ensemble2(const Lattice& L, const EnsLaunch& a);
+// four fused steps per launch (kbc_ensemble4.hip, never persistent); a.rows is a step4_shape code,
+// the table's tiles are 64 x step4_rows(a.rows)
+int launch_ensemble4(const Lattice& L, const EnsLaunch& a);
 
 // adjoint (kbc_adjoint.hip).  An adjoint step writes its per-workgroup
 // dL/dbeta sums as one slice of adjoint_slice_len(L) doubles to `slice`
@@ -136,9 +152,6 @@ int64_t adjoint_slice_len(const Lattice& L);
 int launch_sum_slices(const double* slices, int64_t len, int k, double* tot, double* acc, hipStream_t stream);
 int launch_adjoint_seed(const Lattice& L, const void* state, const double* drho, const double* dux,
                         const double* duy, void* lam);
-// four fused steps per launch (kbc_ensemble4.hip, never persistent); a.rows is a step4_shape code,
-// the table's tiles are 64 x step4_rows(a.rows)
-int launch_ensemble4(const Lattice& L, const EnsLaunch& a);
 // fsrc / fdst (both or neither): one forward step between two other state
 // buffers, run in the same launch as the adjoint step
 int launch_adjoint_step(const Lattice& L, const void* state, const void* lin, void* lout, double* partials,
