@@ -456,13 +456,21 @@ __global__ __launch_bounds__(256) void k_slice_sums(const double* __restrict__ s
     if (threadIdx.x == 0) tot[blockIdx.x] = t;
 }
 
-// acc[0] += tot[n] for n = k-1 down to 0, the order in which the segment's
-// adjoint steps ran: bitwise the same as adding each step's sum after it.
-__global__ void k_add_in_order(const double* __restrict__ tot, int k, double* __restrict__ acc) {
-    if (threadIdx.x != 0) return;
+// acc[0] += tot[n] for n = k-1 down to 0, the order in which the adjoint
+// steps ran: bitwise the same as adding each step's sum after it.  One wave:
+// the lanes load 64 sums at a time, then all of them add those in order (a
+// chain of additions, 2000 of them about 15 us; with a load in the chain it
+// would be a memory latency each).
+__global__ __launch_bounds__(64) void k_add_in_order(const double* __restrict__ tot, int k, double* __restrict__ acc) {
+    const int lane = static_cast<int>(threadIdx.x);
     double a = acc[0];
-    for (int n = k - 1; n >= 0; --n) a += tot[n];
-    acc[0] = a;
+    for (int top = k - 1; top >= 0; top -= 64) {
+        const int n = top - lane;
+        const double v = n >= 0 ? tot[n] : 0.0;
+        const int m = top + 1 < 64 ? top + 1 : 64;
+        for (int i = 0; i < m; ++i) a += __shfl(v, i, 64);
+    }
+    if (lane == 0) acc[0] = a;
 }
 
 }  // namespace

@@ -566,6 +566,16 @@ int ensure_ascratch(lbm_ctx* c, size_t need) {
     c->ascratch_elems = need;
     return LBM_OK;
 }
+
+// lbm_adjoint_init's part of the scratch (after an adjoint step's partials and
+// folds): a partial per 256 nodes and four fields
+size_t init_offset(const lbm_ctx* c) {
+    return static_cast<size_t>(kbc::adjoint_partials(c->L) + kbc::adjoint_slice_len(c->L));
+}
+size_t init_scratch(const lbm_ctx* c) {
+    const size_t N = static_cast<size_t>(c->p.nx) * c->p.ny;
+    return init_offset(c) + (N + 255) / 256 + 4 * N;
+}
 }  // namespace
 
 int lbm_set_adjoint_gamma(lbm_ctx* c, int32_t mode) {
@@ -720,9 +730,17 @@ int lbm_adjoint_rollout(lbm_ctx* c, const void* const* ckpts, int32_t nsteps, in
                 return fail(LBM_EINVAL, "slot %d is NULL or shared by both sets", i);
     }
     const int64_t nb = kbc::adjoint_partials(c->L), ng = kbc::adjoint_slice_len(c->L);
-    const int64_t kr = (static_cast<int64_t>(seglen) + 63) / 64 * 64;
-    int rc = ensure_ascratch(c, static_cast<size_t>(nb + ng * kr + kr));
+    // The steps' dL/dbeta slices are summed once at the end where all of them
+    // take at most 64 MiB (two launches a pass instead of two a segment), else
+    // segment by segment; the order of the additions is the same.
+    const bool once = ng * nsteps <= (int64_t{8} << 20);
+    const int64_t kr = (static_cast<int64_t>(once ? nsteps : seglen) + 63) / 64 * 64;
+    // room for lbm_adjoint_init too, which usually follows: growing the scratch
+    // then would synchronise (0.2 ms in the middle of a backward pass)
+    int rc = ensure_ascratch(c, std::max(static_cast<size_t>(nb + ng * kr + kr), init_scratch(c)));
     if (rc) return rc;
+    double* const slices = c->ascratch + nb;
+    double* const totals = slices + ng * kr;
     void* const* sets[2] = {slots_a, slots_b};
     auto seg_len = [&](int32_t j) { return std::min(seglen, nsteps - j * seglen); };
     // source of recomputed state t + 1 (t = 0 .. k - 2) of segment j
@@ -745,8 +763,8 @@ int lbm_adjoint_rollout(lbm_ctx* c, const void* const* ckpts, int32_t nsteps, in
             const int32_t n = k - 1 - t;
             const void* st = (n == 0) ? ckpts[j] : sets[set][n - 1];
             const bool fwd = t < kn;
-            const int r = kbc::launch_adjoint_step(c->L, st, a, b, c->ascratch,
-                                                   c->ascratch + nb + static_cast<int64_t>(n) * ng, nullptr,
+            const int64_t at = once ? static_cast<int64_t>(j) * seglen + n : n;
+            const int r = kbc::launch_adjoint_step(c->L, st, a, b, c->ascratch, slices + at * ng, nullptr,
                                                    fwd ? fsrc(j - 1, nxt, t) : nullptr, fwd ? sets[nxt][t] : nullptr);
             if (r) return launch_result(r, "lbm_adjoint_rollout");
             std::swap(a, b);
@@ -755,7 +773,13 @@ int lbm_adjoint_rollout(lbm_ctx* c, const void* const* ckpts, int32_t nsteps, in
             const int r = kbc::launch_step(c->L, fsrc(j - 1, nxt, t), sets[nxt][t], c->shape);
             if (r) return launch_result(r, "lbm_adjoint_rollout recompute");
         }
-        const int r = kbc::launch_sum_slices(c->ascratch + nb, ng, k, c->ascratch + nb + ng * kr, dbeta, c->L.stream);
+        if (!once) {
+            const int r = kbc::launch_sum_slices(slices, ng, k, totals, dbeta, c->L.stream);
+            if (r) return launch_result(r, "lbm_adjoint_rollout sum");
+        }
+    }
+    if (once) {
+        const int r = kbc::launch_sum_slices(slices, ng, nsteps, totals, dbeta, c->L.stream);
         if (r) return launch_result(r, "lbm_adjoint_rollout sum");
     }
     *which = (a == lam_in) ? 0 : 1;
@@ -768,11 +792,9 @@ int lbm_adjoint_init(lbm_ctx* c, const double* rho, const double* ux, const doub
         return fail(LBM_EINVAL, "ctx, ux, uy, lam0 and both gradient outputs are required");
     if (mode != LBM_INIT_EQ && mode != LBM_INIT_GRAD_CD)
         return fail(LBM_EUNSUPPORTED, "adjoint of init mode %d is not built", mode);
-    const size_t N = static_cast<size_t>(c->p.nx) * c->p.ny;
-    const size_t nb = (N + 255) / 256;
-    // the adjoint step's partials and folds come first
-    const size_t off = static_cast<size_t>(kbc::adjoint_partials(c->L) + kbc::adjoint_slice_len(c->L));
-    int rc = ensure_ascratch(c, off + nb + 4 * N);
+    const size_t nb = (static_cast<size_t>(c->p.nx) * c->p.ny + 255) / 256;
+    const size_t off = init_offset(c);
+    int rc = ensure_ascratch(c, init_scratch(c));
     if (rc) return rc;
     return launch_result(kbc::launch_adjoint_init(c->L, rho, ux, uy, mode == LBM_INIT_GRAD_CD ? 1 : 0, lam0,
                                                   grad_ux, grad_uy, c->ascratch + off + nb, c->ascratch + off,
@@ -797,6 +819,13 @@ struct lbm_ens {
     int64_t dmap2_len;
     int32_t* dmap;              // member of each single-step tile
     int64_t dmap_len;
+    int default_rows;           // fused tile height the library chose
+    double state_bytes;         // of all members' buffers
+    int shape4;                 // launch shape of four fused steps (0: pairs are as fast)
+    kbc::EnsEntry* dtab4;       // member table, tile count and tile index for it
+    int ntiles4;
+    int32_t* dmap4;
+    int64_t dmap4_len;
     std::vector<uint64_t> gens; // member parameter generations the tables were built from
 };
 
@@ -819,13 +848,6 @@ int64_t ens_table(const lbm_ens* e, int tw, int th, std::vector<kbc::EnsEntry>& 
         t.buf[0] = c->buf[0];
         t.buf[1] = c->buf[1];
         t.nx = c->p.nx;
-    int default_rows;           // fused tile height the library chose
-    double state_bytes;         // of all members' buffers
-    int shape4;                 // launch shape of four fused steps (0: pairs are as fast)
-    kbc::EnsEntry* dtab4;       // member table, tile count and tile index for it
-    int ntiles4;
-    int32_t* dmap4;
-    int64_t dmap4_len;
         t.ny = c->p.ny;
         t.ntx = (c->p.nx + tw - 1) / tw;
         t.pitch = c->L.pitch;
@@ -894,6 +916,25 @@ int ens_build(lbm_ens* e) {
     e->ntiles2 = static_cast<int>(tiles2);
     rc = ens_map(e, tab, tiles2, &e->dmap2, &e->dmap2_len);
     if (rc) return rc;
+    std::vector<int32_t> sizes;
+    for (const lbm_ctx* c : e->m) {
+        sizes.push_back(c->p.nx);
+        sizes.push_back(c->p.ny);
+    }
+    e->shape4 = kbc::step4_shape(e->L, sizes.data(), static_cast<int>(e->m.size()), e->state_bytes, e->shape.nt,
+                                 false);
+    if (e->shape4) {
+        const int64_t tiles4 = ens_table(e, 64, kbc::step4_rows(e->shape4), tab);
+        if (tiles4 < 0 || !kbc::grid_fits(8 * ((tiles4 + 7) / 8), 64 * kbc::step4_waves(e->shape4))) {
+            e->shape4 = 0;
+        } else {
+            rc = ens_upload(e, &e->dtab4, tab);
+            if (rc) return rc;
+            rc = ens_map(e, tab, tiles4, &e->dmap4, &e->dmap4_len);
+            if (rc) return rc;
+            e->ntiles4 = static_cast<int>(tiles4);
+        }
+    }
     ens_table(e, e->shape.width, (256 / e->shape.width) * e->shape.rpt, tab);
     rc = ens_upload(e, &e->dtab, tab);
     if (rc) return rc;
@@ -916,25 +957,6 @@ int lbm_set_halo(lbm_ctx* c, const void* lo, const void* hi) {
     int rc = graph_reset(c);
     if (rc) return rc;
     if (lo) c->graph_chunk = 0;
-    std::vector<int32_t> sizes;
-    for (const lbm_ctx* c : e->m) {
-        sizes.push_back(c->p.nx);
-        sizes.push_back(c->p.ny);
-    }
-    e->shape4 = kbc::step4_shape(e->L, sizes.data(), static_cast<int>(e->m.size()), e->state_bytes, e->shape.nt,
-                                 false);
-    if (e->shape4) {
-        const int64_t tiles4 = ens_table(e, 64, kbc::step4_rows(e->shape4), tab);
-        if (tiles4 < 0 || !kbc::grid_fits(8 * ((tiles4 + 7) / 8), 64 * kbc::step4_waves(e->shape4))) {
-            e->shape4 = 0;
-        } else {
-            rc = ens_upload(e, &e->dtab4, tab);
-            if (rc) return rc;
-            rc = ens_map(e, tab, tiles4, &e->dmap4, &e->dmap4_len);
-            if (rc) return rc;
-            e->ntiles4 = static_cast<int>(tiles4);
-        }
-    }
     c->L.halo_lo = lo;
     c->L.halo_hi = hi;
     return LBM_OK;
@@ -984,7 +1006,13 @@ int lbm_ensemble_create(lbm_ens** out, lbm_ctx* const* members, int32_t count) {
         for (const lbm_ctx* c : e->m)
             state += 2.0 * 9.0 * c->p.ny * static_cast<double>(c->L.pitch) * form_bytes(c->p.form);
         if (plain_stores_pay(m0->p.form, state)) e->shape.nt = 0;
+        e->state_bytes = state;
     }
+    e->shape4 = 0;
+    e->dtab4 = nullptr;
+    e->ntiles4 = 0;
+    e->dmap4 = nullptr;
+    e->dmap4_len = 0;
     e->dtab = nullptr;
     e->dtab2 = nullptr;
     e->dmap2 = nullptr;
@@ -1006,14 +1034,10 @@ int lbm_ensemble_create(lbm_ens** out, lbm_ctx* const* members, int32_t count) {
         if (e->dsync) (void)hipFree(e->dsync);
         if (e->dtab) (void)hipFree(e->dtab);
         if (e->dtab2) (void)hipFree(e->dtab2);
-        e->state_bytes = state;
         if (e->dmap2) (void)hipFree(e->dmap2);
-    e->shape4 = 0;
-    e->dtab4 = nullptr;
-    e->ntiles4 = 0;
-    e->dmap4 = nullptr;
-    e->dmap4_len = 0;
         if (e->dmap) (void)hipFree(e->dmap);
+        if (e->dtab4) (void)hipFree(e->dtab4);
+        if (e->dmap4) (void)hipFree(e->dmap4);
         delete e;
         return rc;
     }
@@ -1036,8 +1060,6 @@ int lbm_ensemble_set_tile(lbm_ens* e, int32_t width, int32_t rows_per_thread, in
 
 int lbm_ensemble_blocks(const lbm_ens* e) {
     if (!e) return fail(LBM_EINVAL, "ensemble is NULL");
-        if (e->dtab4) (void)hipFree(e->dtab4);
-        if (e->dmap4) (void)hipFree(e->dmap4);
     int blocks = 0;
     kbc::EnsLaunch a{};
     a.shape = e->shape;
@@ -1102,6 +1124,17 @@ int lbm_ensemble_step(lbm_ens* e, int32_t nsteps, int32_t persistent) {
     a.stream = e->L.stream;
     a.rows = e->rows;
     int par = cur;
+    if (fours) {
+        a.table = e->dtab4;
+        a.tile_member = e->dmap4;
+        a.ntiles = e->ntiles4;
+        a.nsteps = fours;
+        a.parity = par;
+        a.rows = e->shape4;
+        const int rc = kbc::launch_ensemble4(e->L, a);
+        if (rc) return launch_result(rc, "lbm_ensemble_step (four fused steps)");
+        a.rows = e->rows;
+    }
     if (pairs) {
         a.table = e->dtab2;
         a.tile_member = e->dmap2;
@@ -1124,17 +1157,6 @@ int lbm_ensemble_step(lbm_ens* e, int32_t nsteps, int32_t persistent) {
         const int rc = kbc::launch_ensemble(e->L, a);
         if (rc) return launch_result(rc, "lbm_ensemble_step");
         par ^= (singles & 1);
-    if (fours) {
-        a.table = e->dtab4;
-        a.tile_member = e->dmap4;
-        a.ntiles = e->ntiles4;
-        a.nsteps = fours;
-        a.parity = par;
-        a.rows = e->shape4;
-        const int rc = kbc::launch_ensemble4(e->L, a);
-        if (rc) return launch_result(rc, "lbm_ensemble_step (four fused steps)");
-        a.rows = e->rows;
-    }
     }
     for (lbm_ctx* c : e->m) {
         c->cur = par;
@@ -1173,6 +1195,8 @@ int lbm_ensemble_free(lbm_ens* e) {
         if (e->dtab2) (void)hipFree(e->dtab2);
         if (e->dmap2) (void)hipFree(e->dmap2);
         if (e->dmap) (void)hipFree(e->dmap);
+        if (e->dtab4) (void)hipFree(e->dtab4);
+        if (e->dmap4) (void)hipFree(e->dmap4);
     }
     for (lbm_ctx* c : e->m) --c->ens_refs;
     delete e;
@@ -1185,5 +1209,3 @@ int lbm_copy_probe(void* dst, const void* src, size_t n_words, void* stream) {
 }
 
 }  // extern "C"
-        if (e->dtab4) (void)hipFree(e->dtab4);
-        if (e->dmap4) (void)hipFree(e->dmap4);
