@@ -23,12 +23,6 @@ namespace {
 
 __device__ __forceinline__ int wrapi(int v, int n) { return v < 0 ? v + n : (v >= n ? v - n : v); }
 
-__device__ __forceinline__ double wave_sum_d(double v) {
-#pragma unroll
-    for (int o = 32; o >= 1; o >>= 1) v += __shfl_xor(v, o, 64);
-    return v;
-}
-
 // Sum of one double per thread over the 256-thread block (fixed order).
 __device__ __forceinline__ double block_sum(double v) {
     __shared__ double red[4];
@@ -104,13 +98,17 @@ constexpr int kFold = 2048;   // partials per k_fold workgroup
 // The adjoint step of workgroup index bidx (the 256 threads of the calling
 // workgroup must all call it: it holds a workgroup barrier).  SLAB: rows -1
 // and ny of the state and of the incoming adjoint come from halo buffers
-// (SlabHalo, kbc_tile.hpp) instead of wrapping.
+// (SlabHalo, kbc_tile.hpp) instead of wrapping.  pieces = 0: partials[bidx]
+// receives the workgroup's sum of dL/dbeta terms.  pieces > 0 (the number of
+// 64-node pieces of a row): partials[y * pieces + x / 64] receives the sum of
+// each piece, whatever the tile shape, so that kernels with other tiles (two
+// steps per launch, kbc_adjoint2.hip) give the same sums.
 template <int FORM, int COLL, int VAR, int GM, bool FROZEN, int RPT, bool SLAB = false>
 __device__ __forceinline__ void adj_tile(const typename Form<FORM>::S* __restrict__ state,
                                          const typename Form<FORM>::R* __restrict__ lin,
                                          typename Form<FORM>::R* __restrict__ lout, int nx, int ny,
                                          int64_t pitch, int ntx, int nty, const Coef<typename Form<FORM>::R>& K,
-                                         double* __restrict__ partials, unsigned bidx,
+                                         double* __restrict__ partials, int pieces, unsigned bidx,
                                          const SlabHalo<typename Form<FORM>::S>& sh = {},
                                          const SlabHalo<typename Form<FORM>::R>& lh = {}) {
     using F = Form<FORM>;
@@ -140,7 +138,7 @@ __device__ __forceinline__ void adj_tile(const typename Form<FORM>::S* __restric
     // rows per thread, that row + 2
     const int ya = __builtin_amdgcn_readfirstlane(row * WR + static_cast<int>(threadIdx.x / TW));
     const int yb = ya + 2;
-    double db = 0.0;
+    double dba = 0.0, dbb = 0.0;
     if (u < ntx * rows && x < nx && ya < ny) {
         const uint32_t xm = static_cast<uint32_t>((x == 0) ? nx - 1 : x - 1);
         const uint32_t xp = static_cast<uint32_t>((x == nx - 1) ? 0 : x + 1);
@@ -182,12 +180,12 @@ __device__ __forceinline__ void adj_tile(const typename Form<FORM>::S* __restric
             mu[7] = ld_at(la(ym, 7), xm * sR);
             mu[8] = ld_at(la(ym, 8), xp * sR);
         };
-        auto finish = [&](int yu, const R (&g)[9], const R (&mu)[9]) {
+        auto finish = [&](int yu, const R (&g)[9], const R (&mu)[9]) -> double {
             R lam[9], dbn;
             collide_vjp<R, COLL, VAR, GM, FROZEN>(g, mu, K, lam, dbn);
 #pragma unroll
             for (int i = 0; i < 9; ++i) st_at<false>(row_ptr(lout, yu, i, pitch), x0 * sR, lam[i]);
-            db += static_cast<double>(dbn);
+            return static_cast<double>(dbn);
         };
         R ga[9], ma[9];
         if (RPT == 2 && yb < ny) {
@@ -195,27 +193,42 @@ __device__ __forceinline__ void adj_tile(const typename Form<FORM>::S* __restric
             R gb[9], mb[9];
             load(ya, ga, ma);
             load(yb, gb, mb);
-            finish(ya, ga, ma);
-            finish(yb, gb, mb);
+            // left alone, the scheduler sinks the second row's loads behind the
+            // first row's arithmetic to save registers (335 against 326 us on
+            // 4096^2 FP32)
+            __builtin_amdgcn_sched_barrier(0);
+            dba = finish(ya, ga, ma);
+            dbb = finish(yb, gb, mb);
         } else {
             load(ya, ga, ma);
-            finish(ya, ga, ma);
+            dba = finish(ya, ga, ma);
         }
     }
-    const double s = block_sum(db);
+    if (pieces) {
+        const int piece = col * 2 + static_cast<int>((threadIdx.x >> 6) & 1u);
+        const double sa = wave_sum_d(dba), sb = RPT == 2 ? wave_sum_d(dbb) : 0.0;
+        if (u < ntx * rows && piece < pieces && (threadIdx.x & 63u) == 0) {
+            if (ya < ny) partials[static_cast<int64_t>(ya) * pieces + piece] = sa;
+            if (RPT == 2 && yb < ny) partials[static_cast<int64_t>(yb) * pieces + piece] = sb;
+        }
+        return;
+    }
+    const double s = block_sum(dba + dbb);
     if (threadIdx.x == 0) partials[bidx] = s;
 }
 
+// Five waves per SIMD at most with two rows per thread: with more, the front of
+// resident tiles outgrows what the L2s hold of their shared lines.
 template <int FORM, int COLL, int VAR, int GM, bool FROZEN, int RPT, bool SLAB>
-__global__ __launch_bounds__(256) void k_adj_step(const typename Form<FORM>::S* __restrict__ state,
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, RPT == 2 ? 5 : 8))) void k_adj_step(const typename Form<FORM>::S* __restrict__ state,
                                                   const typename Form<FORM>::R* __restrict__ lin,
                                                   typename Form<FORM>::R* __restrict__ lout, int nx,
                                                   int ny, int64_t pitch, int ntx, int nty,
                                                   Coef<typename Form<FORM>::R> K,
-                                                  double* __restrict__ partials,
+                                                  double* __restrict__ partials, int pieces,
                                                   SlabHalo<typename Form<FORM>::S> sh,
                                                   SlabHalo<typename Form<FORM>::R> lh) {
-    adj_tile<FORM, COLL, VAR, GM, FROZEN, RPT, SLAB>(state, lin, lout, nx, ny, pitch, ntx, nty, K, partials,
+    adj_tile<FORM, COLL, VAR, GM, FROZEN, RPT, SLAB>(state, lin, lout, nx, ny, pitch, ntx, nty, K, partials, pieces,
                                                      blockIdx.x, sh, lh);
 }
 
@@ -233,12 +246,12 @@ __global__ __launch_bounds__(256) void k_adj_step_fwd(const typename Form<FORM>:
                                                       typename Form<FORM>::R* __restrict__ lout, int nx,
                                                       int ny, int64_t pitch, int ntx, int nty,
                                                       Coef<typename Form<FORM>::R> K,
-                                                      double* __restrict__ partials, unsigned nadj,
+                                                      double* __restrict__ partials, int pieces, unsigned nadj,
                                                       const typename Form<FORM>::S* __restrict__ src,
                                                       typename Form<FORM>::S* __restrict__ dst, int ntx_f,
                                                       int ntiles_f, int per_xcd_f) {
     if (blockIdx.x < nadj) {
-        adj_tile<FORM, COLL, VAR, GM, FROZEN, RPT>(state, lin, lout, nx, ny, pitch, ntx, nty, K, partials,
+        adj_tile<FORM, COLL, VAR, GM, FROZEN, RPT>(state, lin, lout, nx, ny, pitch, ntx, nty, K, partials, pieces,
                                                    blockIdx.x);
         return;
     }
@@ -364,12 +377,12 @@ int64_t adj_slice_len(const Lattice& L) {
 template <int FORM, int COLL, int VAR, int GM>
 struct AdjStepOp {
     static int run(const Lattice& L, const void* state, const void* lin, void* lout, double* partials,
-                   double* slice, double* acc, const void* fsrc, void* fdst) {
-        return go(L, state, lin, lout, partials, slice, acc, fsrc, fdst);
+                   double* slice, double* acc, const void* fsrc, void* fdst, int pieces) {
+        return go(L, state, lin, lout, partials, slice, acc, fsrc, fdst, pieces);
     }
     template <bool FROZEN, int RPT>
     static void launch(const Lattice& L, const void* state, const void* lin, void* lout, int ntx, int nty,
-                       int64_t nb, double* out, const void* fsrc, void* fdst) {
+                       int64_t nb, double* out, const void* fsrc, void* fdst, int pieces) {
         using F = Form<FORM>;
         using R = typename F::R;
         using S = typename F::S;
@@ -383,14 +396,14 @@ struct AdjStepOp {
             k_adj_step<FORM, COLL, VAR, GM, FROZEN, RPT, true>
                 <<<dim3(static_cast<unsigned>(nb)), dim3(256), 0, L.stream>>>(
                     static_cast<const S*>(state), static_cast<const R*>(lin), static_cast<R*>(lout), L.nx, L.ny,
-                    L.pitch, ntx, nty, make_coef<R>(L), out, sh, lh);
+                    L.pitch, ntx, nty, make_coef<R>(L), out, pieces, sh, lh);
             return;
         }
         if (!fsrc) {
             k_adj_step<FORM, COLL, VAR, GM, FROZEN, RPT, false>
                 <<<dim3(static_cast<unsigned>(nb)), dim3(256), 0, L.stream>>>(
                     static_cast<const S*>(state), static_cast<const R*>(lin), static_cast<R*>(lout), L.nx, L.ny,
-                    L.pitch, ntx, nty, make_coef<R>(L), out, SlabHalo<S>{}, SlabHalo<R>{});
+                    L.pitch, ntx, nty, make_coef<R>(L), out, pieces, SlabHalo<S>{}, SlabHalo<R>{});
             return;
         }
         // forward part: 256 x 1 tiles, renumbered per XCD as in the step kernel
@@ -400,11 +413,11 @@ struct AdjStepOp {
         const int64_t grid = nb + 8 * static_cast<int64_t>(per_xcd_f);
         k_adj_step_fwd<FORM, COLL, VAR, GM, FROZEN, RPT><<<dim3(static_cast<unsigned>(grid)), dim3(256), 0, L.stream>>>(
             static_cast<const S*>(state), static_cast<const R*>(lin), static_cast<R*>(lout), L.nx, L.ny, L.pitch,
-            ntx, nty, make_coef<R>(L), out, static_cast<unsigned>(nb), static_cast<const S*>(fsrc),
+            ntx, nty, make_coef<R>(L), out, pieces, static_cast<unsigned>(nb), static_cast<const S*>(fsrc),
             static_cast<S*>(fdst), ntx_f, ntiles_f, per_xcd_f);
     }
     static int go(const Lattice& L, const void* state, const void* lin, void* lout, double* partials,
-                  double* slice, double* acc, const void* fsrc, void* fdst) {
+                  double* slice, double* acc, const void* fsrc, void* fdst, int pieces) {
         const int rpt = adj_rows_per_thread(L);
         const int ntx = (L.nx + 127) / 128, nty = (L.ny + 2 * rpt - 1) / (2 * rpt);
         const int64_t nb = adj_blocks(L);
@@ -413,28 +426,29 @@ struct AdjStepOp {
         if (L.adj_halo[0] && fsrc) return -1;   // a slab's adjoint step runs alone
         // the fused forward part needs its grid to fit next to the adjoint's
         if (fsrc && !grid_fits(static_cast<int64_t>((L.nx + 255) / 256) * L.ny + 8 + nb, 256)) return kTooLarge;
-        const bool direct = nb <= kDirect;
+        const int64_t np = pieces ? static_cast<int64_t>(pieces) * L.ny : nb;   // partial sums written
+        const bool direct = np <= kDirect;
         if (!slice || (!direct && !partials)) return -1;
         double* out = direct ? slice : partials;
         if constexpr (FORM == F64) {
             if (rpt != 1) return -1;
             if (L.adj_frozen)
-                launch<true, 1>(L, state, lin, lout, ntx, nty, nb, out, fsrc, fdst);
+                launch<true, 1>(L, state, lin, lout, ntx, nty, nb, out, fsrc, fdst, pieces);
             else
-                launch<false, 1>(L, state, lin, lout, ntx, nty, nb, out, fsrc, fdst);
+                launch<false, 1>(L, state, lin, lout, ntx, nty, nb, out, fsrc, fdst, pieces);
         } else {
             if (L.adj_frozen) {
-                if (rpt == 2) launch<true, 2>(L, state, lin, lout, ntx, nty, nb, out, fsrc, fdst);
-                else launch<true, 1>(L, state, lin, lout, ntx, nty, nb, out, fsrc, fdst);
+                if (rpt == 2) launch<true, 2>(L, state, lin, lout, ntx, nty, nb, out, fsrc, fdst, pieces);
+                else launch<true, 1>(L, state, lin, lout, ntx, nty, nb, out, fsrc, fdst, pieces);
             } else {
-                if (rpt == 2) launch<false, 2>(L, state, lin, lout, ntx, nty, nb, out, fsrc, fdst);
-                else launch<false, 1>(L, state, lin, lout, ntx, nty, nb, out, fsrc, fdst);
+                if (rpt == 2) launch<false, 2>(L, state, lin, lout, ntx, nty, nb, out, fsrc, fdst, pieces);
+                else launch<false, 1>(L, state, lin, lout, ntx, nty, nb, out, fsrc, fdst, pieces);
             }
         }
         if (ok()) return -2;
-        const int64_t len = adj_slice_len(L);
+        const int64_t len = direct ? np : (np + kFold - 1) / kFold;
         if (!direct) {
-            k_fold<<<dim3(static_cast<unsigned>(len)), dim3(256), 0, L.stream>>>(partials, nb, slice);
+            k_fold<<<dim3(static_cast<unsigned>(len)), dim3(256), 0, L.stream>>>(partials, np, slice);
             if (ok()) return -2;
         }
         if (acc) {
@@ -501,8 +515,23 @@ int launch_adjoint_seed(const Lattice& L, const void* state, const double* drho,
 }
 
 int launch_adjoint_step(const Lattice& L, const void* state, const void* lin, void* lout, double* partials,
-                        double* slice, double* acc, const void* fsrc, void* fdst) {
-    return dispatch<AdjStepOp>(L, state, lin, lout, partials, slice, acc, fsrc, fdst);
+                        double* slice, double* acc, const void* fsrc, void* fdst, int pieces) {
+    return dispatch<AdjStepOp>(L, state, lin, lout, partials, slice, acc, fsrc, fdst, pieces);
+}
+
+int adjoint_pieces(const Lattice& L) { return (L.nx + 63) / 64; }
+int64_t adjoint_piece_partials(const Lattice& L) {
+    const int64_t np = static_cast<int64_t>(adjoint_pieces(L)) * L.ny;
+    return np <= kDirect ? 0 : 2 * np;
+}
+int64_t adjoint_piece_slice(const Lattice& L) {
+    const int64_t np = static_cast<int64_t>(adjoint_pieces(L)) * L.ny;
+    return np <= kDirect ? np : (np + kFold - 1) / kFold;
+}
+int launch_fold_pieces(const Lattice& L, const double* partials, double* slice) {
+    const int64_t np = static_cast<int64_t>(adjoint_pieces(L)) * L.ny;
+    k_fold<<<dim3(static_cast<unsigned>((np + kFold - 1) / kFold)), dim3(256), 0, L.stream>>>(partials, np, slice);
+    return ok();
 }
 
 int launch_adjoint_init(const Lattice& L, const double* rho, const double* ux, const double* uy, int mode,

@@ -19,22 +19,31 @@
 
 namespace kbc {
 
-// Adjoint of the map from a zero-mass, zero-momentum moment vector (T, N, Pi,
-// Q_xyy, Q_yxx, A) to populations, eq. (momentsD2Q9) (the map kbc_forward
-// applies to the 1/4-scaled moments): moment adjoints from population
-// adjoints pb.
+// Sum of one double per lane over the wave, in a fixed order.
+__device__ __forceinline__ double wave_sum_d(double v) {
+#pragma unroll
+    for (int o = 32; o >= 1; o >>= 1) v += __shfl_xor(v, o, 64);
+    return v;
+}
+
+// Moment adjoints from the adjoints p of populations in kbc_forward's scaled
+// units: of T, N, Pi and of half of Q_xyy, Q_yxx and A.
+template <typename R> struct MomAdj {
+    R T, N, P, x, y, a;
+};
 template <typename R>
-__device__ __forceinline__ void pop_to_moments_adj(const R (&pb)[9], R& Tb, R& Nb, R& Pb, R& Qxb,
-                                                   R& Qyb, R& Ab) {
-    const R q = R(0.25), h = R(0.5);
-    const R ax = pb[1] + pb[3], ay = pb[2] + pb[4];
-    const R dg = (pb[5] + pb[7]) + (pb[6] + pb[8]);
-    Tb = q * (ax + ay) - pb[0];
-    Nb = q * (ax - ay);
-    Pb = q * ((pb[5] + pb[7]) - (pb[6] + pb[8]));
-    Qxb = h * (pb[3] - pb[1]) + q * ((pb[5] - pb[7]) - (pb[6] - pb[8]));
-    Qyb = h * (pb[4] - pb[2]) + q * ((pb[5] - pb[7]) + (pb[6] - pb[8]));
-    Ab = pb[0] - h * (ax + ay) + q * dg;
+__device__ __forceinline__ MomAdj<R> moments_adj(const R (&p)[9]) {
+    MomAdj<R> m;
+    const R a1 = p[1] + p[3], a2 = p[2] + p[4], f57 = p[5] + p[7], f68 = p[6] + p[8];
+    const R e57 = p[5] - p[7], e86 = p[8] - p[6];
+    const R ax = a1 + a2;
+    m.T = fmaR(R(0.25), ax, R(-0.5) * p[0]);
+    m.N = R(0.25) * (a1 - a2);
+    m.P = R(0.5) * (f57 - f68);
+    m.x = (p[3] - p[1]) + (e57 + e86);
+    m.y = (p[4] - p[2]) + (e57 - e86);
+    m.a = (p[0] - ax) + (f57 + f68);
+    return m;
 }
 
 // FROZEN = true holds gamma at its forward value (the derivative of the map
@@ -95,15 +104,11 @@ __device__ __forceinline__ void collide_vjp(const R (&g)[9], const R (&mu)[9], c
     } else {
         KbcNode<R> n;
         kbc_forward<R, VAR, (GM == GEXACT ? GEST : GM)>(g, K, n);
-        const R third = R(1.0 / 3.0), ninth = R(1.0 / 9.0);
+        constexpr bool kCentral = (VAR == VA || VAR == VB), kTrace = (VAR == VA || VAR == VC);
+        constexpr R third = R(1.0 / 3.0);
         ir = n.ir;
         ux = n.ux;
         uy = n.uy;
-        const R jx = n.jx, jy = n.jy, uxx = n.uxx, uyy = uy * uy, u2 = n.u2;
-        const R dN = n.dN, dP = n.dP, tT = n.tT;
-        R ds[9], dh[9], w[9];
-        unscaled(n, ds, dh, w);
-        const R ratio = n.ratio, bsum = n.b;
         const bool active = n.active;
         R gam = n.gam;
         if constexpr (GM == GEXACT) {
@@ -111,30 +116,29 @@ __device__ __forceinline__ void collide_vjp(const R (&g)[9], const R (&mu)[9], c
         }
 
         // --------------------------------------------------------- reverse
-        // (mul + add pairs below may fuse: nothing else is computed from
-        // these values, so there is no bitwise contract to keep)
-        {
-#pragma clang fp contract(fast)
-            // g'_i = g_i - 2 beta ds_i - beta gamma dh_i
-            // d g'_i / d beta = -(2 ds_i + gamma dh_i): mu . dg'/dbeta is
-            // -(2 mu.ds + gamma mu.dh), and mu.dh also gives gamma's adjoint
-            R dsb[9], dhb[9];
-            R mdh = R(0), mds = R(0);
-            const R tb = R(2) * K.beta, bg = K.beta * gam;
-    #pragma unroll
-            for (int i = 0; i < 9; ++i) {
-                lam[i] = mu[i];
-                dsb[i] = -tb * mu[i];
-                dhb[i] = -bg * mu[i];
-                mdh = fmaR(mu[i], dh[i], mdh);
-                mds = fmaR(mu[i], ds[i], mds);
-            }
-            R gamb = -K.beta * mdh;
-            dbeta = -fmaR(gam, mdh, R(2) * mds);
-            if constexpr (GM != GFIX && !FROZEN) {
+        // g'_i = g_i - 2 beta s_i - beta gamma h_i; m_i, sb_i and hb_i are
+        // adjoints of the scaled populations s_i node_scale(i), h_i node_scale(i)
+        R m[9], sb[9], hb[9];
+        R mdh = R(0), mds = R(0);
+        const R tb = R(2) * K.beta, bg = K.beta * gam;
+#pragma unroll
+        for (int i = 0; i < 9; ++i) {
+            lam[i] = mu[i];
+            m[i] = (i == 0 || i > 4) ? mu[i] * (R(1) / node_scale<R>(i)) : mu[i];
+            mdh = fmaR(m[i], n.dh[i], mdh);
+            if (VAR != VD || i) mds = fmaR(m[i], n.ds[i], mds);
+            sb[i] = -tb * m[i];
+            hb[i] = -bg * m[i];
+        }
+        // d g'_i / d beta = -(2 s_i + gamma h_i), d g'_i / d gamma = -beta h_i
+        const R gamb = -K.beta * mdh;
+        dbeta = -fmaR(gam, mdh, R(2) * mds);
+        if constexpr (GM != GFIX && !FROZEN) {
+            R wd[9];                                   // adjoints of the scaled denominators d_i
+            if constexpr (GM == GEXACT) {
+#pragma unroll
+                for (int i = 0; i < 9; ++i) wd[i] = R(0);
                 if (active) {
-                    R wd[9];                                   // adjoint of d_i
-                    if constexpr (GM == GEXACT) {
                     // F = sum_i dh_i ln(1 + x_i), x_i = y_i wr_i,
                     // y_i = (1 - beta gamma) dh_i - (2 beta - 1) ds_i, wr_i = w_i / rho:
                     // dF/d dh_i = ln(1 + x_i) + (1 - beta gamma) dh_i wr_i / (1 + x_i),
@@ -142,14 +146,16 @@ __device__ __forceinline__ void collide_vjp(const R (&g)[9], const R (&mu)[9], c
                     // dF/d wr_i = dh_i y_i / (1 + x_i),
                     // dF/d beta = -sum_i dh_i (gamma dh_i + 2 ds_i) wr_i / (1 + x_i),
                     // F'(gamma) = -beta sum_i dh_i^2 wr_i / (1 + x_i)
+                    R ds[9], dh[9], w[9];
+                    unscaled(n, ds, dh, w);
                     const R om = R(1) - K.beta * gam, tbm1 = R(2) * K.beta - R(1);
                     R wr[9], y[9], r[9], lg[9];
                     R D = R(0);
                     bool ok = true;
-    #pragma unroll
+#pragma unroll
                     for (int i = 0; i < 9; ++i) {
                         wr[i] = w[i] * ir;
-                        y[i] = om * dh[i] - tbm1 * ds[i];
+                        y[i] = fmaR(om, dh[i], -(tbm1 * ds[i]));
                         const R x = y[i] * wr[i];
                         ok = ok && (x > R(-1));
                         r[i] = rcpR(R(1) + x);
@@ -160,85 +166,86 @@ __device__ __forceinline__ void collide_vjp(const R (&g)[9], const R (&mu)[9], c
                     // of the logarithm left (0, inf), or F' >= 0) gamma is held
                     const R imp = (ok && D < R(0)) ? -gamb / D : R(0);   // -gamma_bar / F'
                     R irb = R(0), fb = R(0);
-    #pragma unroll
+#pragma unroll
                     for (int i = 0; i < 9; ++i) {
+                        const R k = R(1) / node_scale<R>(i), k2 = k * k;
                         const R t = dh[i] * wr[i] * r[i];
-                        dhb[i] = fmaR(imp, fmaR(om, t, lg[i]), dhb[i]);
-                        dsb[i] = fmaR(imp, -tbm1 * t, dsb[i]);
+                        hb[i] = fmaR(imp * k, fmaR(om, t, lg[i]), hb[i]);
+                        sb[i] = fmaR(imp * k, -tbm1 * t, sb[i]);
                         const R wrb = imp * dh[i] * y[i] * r[i];
                         irb = fmaR(wrb, w[i], irb);
-                        wd[i] = -(wrb * ir) * w[i] * w[i];
+                        wd[i] = -(wrb * ir) * w[i] * w[i] * k2;
                         fb = fmaR(t, fmaR(gam, dh[i], R(2) * ds[i]), fb);
                     }
                     dbeta = fmaR(-imp, fb, dbeta);
-                    drb -= irb * ir * ir;                      // ir = 1 / (rho0 + dr)
-                    } else {
-                    // gamma = 1/beta - (2 - 1/beta) a / b
-                    const R ib2 = K.inv_beta * K.inv_beta;
-                    dbeta = fmaR(gamb, -(R(1) + ratio) * ib2, dbeta);
-                    const R rb = -K.two_m_inv_beta * gamb;     // adjoint of a / b
-                    const R ab = rb * rcpR(bsum);              // adjoint of a
-                    const R bb = -ab * ratio;                  // adjoint of b = -rb a / b^2
-    #pragma unroll
-                    for (int i = 0; i < 9; ++i) {
-                        // a = sum ds dh w, b = sum dh dh w (c enters the guard only);
-                        // the adjoint of w_i is dh_i (ab ds_i + bb dh_i), w_i = 1 / d_i
-                        const R hw = dh[i] * w[i];
-                        const R bh = bb * dh[i];
-                        const R t = fmaR(ab, ds[i], bh);
-                        dsb[i] = fmaR(ab, hw, dsb[i]);
-                        dhb[i] = fmaR(t + bh, w[i], dhb[i]);
-                        wd[i] = -(hw * t) * w[i];
-                    }
-                    }
-                    // d_i in u: 4/9 - 2|u|^2/3; 1/9 - |u|^2/6 + u_a^2/2 +- u_a/3 (axes);
-                    // 1/36 + |u|^2/12 +- u_x u_y/4 + (c.u)/12 (diagonals)
-                    const R p57 = wd[5] + wd[7], p68 = wd[6] + wd[8];
-                    const R e0 = fmaR(R(1.0 / 6.0), p57 + p68, R(-4.0 / 3.0) * wd[0]);
-                    const R p13 = wd[1] + wd[3], p24 = wd[2] + wd[4];
-                    const R cx = fmaR(R(2.0 / 3.0), p13, fmaR(R(-1.0 / 3.0), p24, e0));
-                    const R cy = fmaR(R(-1.0 / 3.0), p13, fmaR(R(2.0 / 3.0), p24, e0));
-                    const R dq = R(0.25) * (p57 - p68);
-                    const R m57 = wd[5] - wd[7], m86 = wd[8] - wd[6];
-                    uxb += fmaR(ux, cx, fmaR(uy, dq, fmaR(R(1.0 / 3.0), wd[1] - wd[3], R(1.0 / 12.0) * (m57 + m86))));
-                    uyb += fmaR(uy, cy, fmaR(ux, dq, fmaR(R(1.0 / 3.0), wd[2] - wd[4], R(1.0 / 12.0) * (m57 - m86))));
+                    drb = -(irb * ir) * ir;                    // ir = 1 / (rho0 + dr)
+                }
+            } else {
+                // gamma = 1/beta - (2 - 1/beta) a / b with a = sum s h w, b = sum h h w
+                // (c enters the guard only); ab, bb: adjoints of a and b, zero where
+                // the guard holds gamma at 2
+                const R ib2 = K.inv_beta * K.inv_beta;
+                const R gb = active ? gamb : R(0);
+                const R ratio = active ? n.ratio : R(0);
+                dbeta = fmaR(gb, -(R(1) + ratio) * ib2, dbeta);
+                const R ab = active ? -K.two_m_inv_beta * gb * rcpR(n.b) : R(0);
+                const R bb = -ab * ratio;
+#pragma unroll
+                for (int i = 0; i < 9; ++i) {
+                    // adjoint of w_i = 1 / d_i: h_i (ab s_i + bb h_i)
+                    const R hw = n.dh[i] * n.w[i];
+                    R q = bb * hw;
+                    if (VAR != VD || i) q = fmaR(ab, n.ds[i] * n.w[i], q);
+                    sb[i] = fmaR(ab, hw, sb[i]);
+                    hb[i] += fmaR(bb, hw, q);
+                    wd[i] = -hw * q;
                 }
             }
-            // ds = P(Ts, dN, dP, Qxs, Qys, As), dh = P(dT - Ts, 0, 0, dQx - Qxs, dQy - Qys, dA - As)
-            R sTb, sNb, sPb, sQxb, sQyb, sAb, hTb, hNb, hPb, hQxb, hQyb, hAb;
-            pop_to_moments_adj<R>(dsb, sTb, sNb, sPb, sQxb, sQyb, sAb);
-            pop_to_moments_adj<R>(dhb, hTb, hNb, hPb, hQxb, hQyb, hAb);
-            R dTb = hTb, dNb = sNb, dPb = sPb, dQxb = hQxb, dQyb = hQyb, dAb = hAb;
-            const R Tsb = sTb - hTb, Qxsb = sQxb - hQxb, Qysb = sQyb - hQyb, Asb = sAb - hAb;
-            if constexpr (VAR == VC) {
-                dTb += Tsb;
-            } else if constexpr (VAR == VA || VAR == VB) {
-                if constexpr (VAR == VA) dTb += Tsb + R(0.5) * (ux * Qxsb + uy * Qysb + u2 * Asb);
-                dNb += R(0.5) * (uy * Qysb - ux * Qxsb - (uxx - uyy) * Asb);
-                dPb += R(2) * (uy * Qxsb + ux * Qysb) + R(4) * ux * uy * Asb;
-                uxb += R(0.5) * (tT - dN) * Qxsb + R(2) * dP * Qysb + (R(4) * uy * dP + ux * (tT - dN)) * Asb;
-                uyb += R(2) * dP * Qxsb + R(0.5) * (tT + dN) * Qysb + (R(4) * ux * dP + uy * (tT + dN)) * Asb;
-            }
-            // dT = dPxx + dPyy, dN = dPxx - dPyy, dP = dPxy
-            const R dPxxb = dTb + dNb, dPyyb = dTb - dNb, dPxyb = dPb;
-            // moments of g - feq
-            Sxxb = dPxxb;
-            Syyb = dPyyb;
-            Sxyb = dPxyb;
-            Qxrb = dQxb;
-            Qyrb = dQyb;
-            Arb = dAb;
-            drb += -(dPxxb + dPyyb) * third - dAb * ninth;
-            jxb += -dPxxb * ux - dPxyb * uy - dQxb * third - dAb * ux * third;
-            jyb += -dPyyb * uy - dQyb * third - dAb * uy * third;
-            uxb += -dPxxb * jx - dAb * jx * third;
-            uyb += -dPyyb * jy - dPxyb * jx - dAb * jy * third;
+            // d_i in u: a quarter of the rest population's 1/9 - |u|^2 / 6, axes
+            // 1/9 - |u|^2 / 6 + u_a^2 / 2 +- u_a / 3, four times the diagonals'
+            // 1/9 + |u|^2 / 3 +- u_x u_y + (c.u) / 3
+            const R p13 = wd[1] + wd[3], p24 = wd[2] + wd[4], p57 = wd[5] + wd[7], p68 = wd[6] + wd[8];
+            const R m57 = wd[5] - wd[7], m86 = wd[8] - wd[6];
+            const R pd = p57 + p68, dq = p57 - p68;
+            const R cx = fmaR(R(2), p13 + pd, -(p24 + wd[0])), cy = fmaR(R(2), p24 + pd, -(p13 + wd[0]));
+            uxb = fmaR(third, fmaR(ux, cx, (wd[1] - wd[3]) + (m57 + m86)), uy * dq);
+            uyb = fmaR(third, fmaR(uy, cy, (wd[2] - wd[4]) + (m57 - m86)), ux * dq);
         }
+        const MomAdj<R> sm = moments_adj<R>(sb), hm = moments_adj<R>(hb);
+        R Tb = kTrace ? sm.T : hm.T, Nb = sm.N, Pb = sm.P;
+        if constexpr (kCentral) {
+            // h = df - s takes Q and A less the shear part's: ox, oy, a2 (the
+            // halves of Q_s, A_s), a2 = u_x ox + u_y oy, ox = u_y Pi + u_x (T_s - N) / 4,
+            // oy = u_x Pi + u_y (T_s + N) / 4
+            const R a2b = sm.a - hm.a;
+            const R oxb = fmaR(ux, a2b, sm.x - hm.x), oyb = fmaR(uy, a2b, sm.y - hm.y);
+            Pb = fmaR(uy, oxb, fmaR(ux, oyb, Pb));
+            const R tm = ux * oxb, tp = uy * oyb;
+            Nb = fmaR(R(0.25), tp - tm, Nb);
+            if constexpr (kTrace) Tb = fmaR(R(0.25), tp + tm, Tb);
+            uxb = fmaR(a2b, n.ox, fmaR(n.tmn, oxb, fmaR(n.dP, oyb, uxb)));
+            uyb = fmaR(a2b, n.oy, fmaR(n.dP, oxb, fmaR(n.tpn, oyb, uyb)));
+        }
+        Qxrb = R(0.5) * hm.x;
+        Qyrb = R(0.5) * hm.y;
+        Arb = R(0.5) * hm.a;
+        // dT = sum c^2 g - 2/3 dr - rho |u|^2, dN = ... - rho (u_x^2 - u_y^2),
+        // dP = ... - rho u_x u_y, dQ_a = ... - j_a / 3, dA = ... - dr / 9 - rho |u|^2 / 3
+        const R J = fmaR(third, Arb, Tb);
+        const R Cx = J + Nb, Cy = J - Nb;
+        jxb = -fmaR(Cx, ux, fmaR(Pb, uy, third * Qxrb));
+        jyb = -fmaR(Cy, uy, third * Qyrb);
+        uxb = fmaR(-Cx, n.jx, uxb);
+        uyb = fmaR(-Cy, n.jy, fmaR(-Pb, n.jx, uyb));
+        drb -= fmaR(R(2.0 / 3.0), Tb, R(1.0 / 9.0) * Arb);
+        Sxxb = Tb + Nb;
+        Syyb = Tb - Nb;
+        Sxyb = Pb;
     }
     // u = j / rho, rho = rho0 + dr
     jxb = fmaR(uxb, ir, jxb);
     jyb = fmaR(uyb, ir, jyb);
-    drb -= (uxb * ux + uyb * uy) * ir;
+    drb = fmaR(-ir, fmaR(uxb, ux, uyb * uy), drb);
     // dr = sum g, j = sum c g, and the raw sums of g:
     // lam_i += drb + c_x jxb + c_y jyb + c_x^2 Sxxb + c_y^2 Syyb + c_x c_y Sxyb
     //          + c_x c_y^2 Qxrb + c_x^2 c_y Qyrb + c_x^2 c_y^2 Arb

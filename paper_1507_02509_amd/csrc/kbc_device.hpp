@@ -140,7 +140,7 @@ template <typename R> struct KbcNode {
     R dr, rho, ir, jx, jy;              // rho - rho0, rho, 1 / rho, rho u
     R ux, uy, uxx, u2;
     R dT, dN, dP;                       // non-equilibrium T, N, Pi
-    R tT;                               // T of the shear part: dT (A, C) or 0 (B, D)
+    R tpn, tmn, ox, oy;                 // of the shear part: (T_s +- N) / 4, Q_xyy,s / 2, Q_yxx,s / 2
     R ds[9], dh[9];                     // shear and higher-order parts of f - feq (scaled)
     R w[9];                             // rho / feq_i (entropic weights, scaled)
     R ratio, b;                         // <ds|dh> / <dh|dh> and <dh|dh>
@@ -198,7 +198,6 @@ __device__ __forceinline__ void kbc_forward(const R (&g)[9], const Coef<R>& K, K
     const R dQy = fmaR(R(-1.0 / 3.0), jy, pq);
     const R dA = fmaR(R(-1.0 / 3.0), jsum, fmaR(R(-1.0 / 9.0), dr, sd));
     n.dT = dT; n.dN = dN; n.dP = dP;
-    n.tT = kTrace ? dT : R(0);
 
     // Shear part s, Table kbc_moment_grouping, from (T_s +- N) / 4, Q_xyy,s / 2
     // (ox), Q_yxx,s / 2 (oy) and A_s / 2 (a2).  Central variants take the
@@ -208,12 +207,16 @@ __device__ __forceinline__ void kbc_forward(const R (&g)[9], const Coef<R>& K, K
     const R tq = R(0.25) * dT;
     const R tpn = kTrace ? tq + n4 : n4, tmn = kTrace ? tq - n4 : -n4;
     const R p2 = R(0.5) * dP;
+    n.tpn = tpn;
+    n.tmn = tmn;
     R (&ds)[9] = n.ds;
     R ox = R(0), oy = R(0), a2 = R(0);
     if constexpr (kCentral) {
         ox = fmaR(uy, dP, ux * tmn);
         oy = fmaR(ux, dP, uy * tpn);
         a2 = fmaR(ux, ox, uy * oy);
+        n.ox = ox;
+        n.oy = oy;
         const R e1 = tpn - a2, e2 = tmn - a2;
         ds[0] = kTrace ? fmaR(R(-0.5), dT, a2) : a2;
         ds[1] = e1 - ox;

@@ -155,7 +155,24 @@ int launch_adjoint_seed(const Lattice& L, const void* state, const double* drho,
 // fsrc / fdst (both or neither): one forward step between two other state
 // buffers, run in the same launch as the adjoint step
 int launch_adjoint_step(const Lattice& L, const void* state, const void* lin, void* lout, double* partials,
-                        double* slice, double* acc, const void* fsrc = nullptr, void* fdst = nullptr);
+                        double* slice, double* acc, const void* fsrc = nullptr, void* fdst = nullptr,
+                        int pieces = 0);
+// With pieces = adjoint_pieces(L) (the 64-node pieces of a row) the partial sums
+// are those of every piece instead, which every launch shape forms alike;
+// scratch of adjoint_piece_partials(L) and slices of adjoint_piece_slice(L)
+// doubles take the place of the two above.  launch_adjoint_pair (kbc_adjoint2.hip)
+// runs two adjoint steps, with state_b = f^{n+1}, state_a = f^n and lin =
+// lambda^{n+2}, into lout = lambda^n and a slice each; fsrc, fmid and fdst (all,
+// or fsrc and fdst for one step, or none) are states of a forward recomputation
+// run in the same launch.  Returns -5 for collisions it is not built for
+// (adjoint_pairs(L) says so before).
+int adjoint_pieces(const Lattice& L);
+int64_t adjoint_piece_partials(const Lattice& L);
+int64_t adjoint_piece_slice(const Lattice& L);
+int launch_fold_pieces(const Lattice& L, const double* partials, double* slice);
+bool adjoint_pairs(const Lattice& L);
+int launch_adjoint_pair(const Lattice& L, const void* state_b, const void* state_a, const void* lin, void* lout,
+                        double* partials, double* slice_b, double* slice_a, const void* fsrc, void* fmid, void* fdst);
 int launch_adjoint_init(const Lattice& L, const double* rho, const double* ux, const double* uy, int mode,
                         const void* lam0, double* gux, double* guy, double* P, double* partials,
                         int64_t nblocks_cap, double* acc);
