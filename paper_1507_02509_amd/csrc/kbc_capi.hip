@@ -686,7 +686,9 @@ int lbm_adjoint_segment(lbm_ctx* c, const void* state0, void* const* slots, int3
     // every adjoint step of the segment writes its dL/dbeta partials to a
     // slice of its own; one reduction at the end adds the slices, in step
     // order, to *dbeta
-    const int64_t nb = kbc::adjoint_partials(c->L), ng = kbc::adjoint_slice_len(c->L);
+    const int64_t nb = kbc::adjoint_piece_partials(c->L), ng = kbc::adjoint_piece_slice(c->L);
+    const int pieces = kbc::adjoint_pieces(c->L);
+    const bool pairs = kbc::adjoint_pairs(c->L);
     // room for k rounded up to 64 slices, so that segments of different
     // lengths in one backward pass do not reallocate (which synchronises)
     const int64_t kr = (static_cast<int64_t>(k) + 63) / 64 * 64;
@@ -700,14 +702,20 @@ int lbm_adjoint_segment(lbm_ctx* c, const void* state0, void* const* slots, int3
     }
     void* a = lam_in;
     void* b = lam_out;
-    for (int32_t n = k - 1; n >= 0; --n) {
-        const void* st = (n == 0) ? state0 : slots[n - 1];
-        rc = kbc::launch_adjoint_step(c->L, st, a, b, c->ascratch, c->ascratch + nb + static_cast<int64_t>(n) * ng,
-                                      nullptr);
+    double* const slices = c->ascratch + nb;
+    auto state = [&](int32_t n) -> const void* { return n == 0 ? state0 : slots[n - 1]; };
+    for (int32_t n = k - 1; n >= 0;) {
+        if (pairs && n > 0) {
+            rc = kbc::launch_adjoint_pair(c->L, state(n), state(n - 1), a, b, c->ascratch, slices + n * ng,
+                                          slices + (n - 1) * ng, nullptr, nullptr, nullptr);
+            n -= 2;
+        } else {
+            rc = kbc::launch_adjoint_step(c->L, state(n), a, b, c->ascratch, slices + n * ng, nullptr, nullptr, nullptr,
+                                          pieces);
+            --n;
+        }
         if (rc) return launch_result(rc, "lbm_adjoint_segment");
-        void* t = a;
-        a = b;
-        b = t;
+        std::swap(a, b);
     }
     rc = kbc::launch_sum_slices(c->ascratch + nb, ng, k, c->ascratch + nb + ng * kr, dbeta, c->L.stream);
     if (rc) return launch_result(rc, "lbm_adjoint_segment sum");
@@ -729,7 +737,9 @@ int lbm_adjoint_rollout(lbm_ctx* c, const void* const* ckpts, int32_t nsteps, in
             if (!slots_a[i] || !slots_b[i] || slots_a[i] == slots_b[i])
                 return fail(LBM_EINVAL, "slot %d is NULL or shared by both sets", i);
     }
-    const int64_t nb = kbc::adjoint_partials(c->L), ng = kbc::adjoint_slice_len(c->L);
+    const int64_t nb = kbc::adjoint_piece_partials(c->L), ng = kbc::adjoint_piece_slice(c->L);
+    const int pieces = kbc::adjoint_pieces(c->L);
+    const bool pairs = kbc::adjoint_pairs(c->L);
     // The steps' dL/dbeta slices are summed once at the end where all of them
     // take at most 64 MiB (two launches a pass instead of two a segment), else
     // segment by segment; the order of the additions is the same.
@@ -756,21 +766,34 @@ int lbm_adjoint_rollout(lbm_ctx* c, const void* const* ckpts, int32_t nsteps, in
         const int set = (nseg - 1 - j) & 1, nxt = set ^ 1;
         const int32_t k = seg_len(j);
         const int32_t kn = (j > 0) ? seg_len(j - 1) - 1 : 0;   // states to recompute for segment j - 1
-        // adjoint step t of the segment runs backward from n = k - 1; the
-        // same launch recomputes state t + 1 of segment j - 1 into the other
-        // slot set (read by nothing in this segment)
-        for (int32_t t = 0; t < k; ++t) {
-            const int32_t n = k - 1 - t;
-            const void* st = (n == 0) ? ckpts[j] : sets[set][n - 1];
-            const bool fwd = t < kn;
-            const int64_t at = once ? static_cast<int64_t>(j) * seglen + n : n;
-            const int r = kbc::launch_adjoint_step(c->L, st, a, b, c->ascratch, slices + at * ng, nullptr,
-                                                   fwd ? fsrc(j - 1, nxt, t) : nullptr, fwd ? sets[nxt][t] : nullptr);
+        // the adjoint steps run backward from n = k - 1, two to a launch; the
+        // same launches recompute the states of segment j - 1 into the other
+        // slot set (read by nothing in this segment), f of them so far
+        auto state = [&](int32_t n) -> const void* { return n == 0 ? ckpts[j] : sets[set][n - 1]; };
+        const int64_t at = once ? static_cast<int64_t>(j) * seglen : 0;
+        int32_t f = 0;
+        for (int32_t n = k - 1; n >= 0;) {
+            const void* src = f < kn ? fsrc(j - 1, nxt, f) : nullptr;
+            void* first = f < kn ? sets[nxt][f] : nullptr;
+            int r;
+            if (pairs && n > 0) {
+                void* second = f + 1 < kn ? sets[nxt][f + 1] : nullptr;
+                r = kbc::launch_adjoint_pair(c->L, state(n), state(n - 1), a, b, c->ascratch, slices + (at + n) * ng,
+                                             slices + (at + n - 1) * ng, src, second ? first : nullptr,
+                                             second ? second : first);
+                f += second ? 2 : (first ? 1 : 0);
+                n -= 2;
+            } else {
+                r = kbc::launch_adjoint_step(c->L, state(n), a, b, c->ascratch, slices + (at + n) * ng, nullptr, src,
+                                             first, pieces);
+                f += first ? 1 : 0;
+                --n;
+            }
             if (r) return launch_result(r, "lbm_adjoint_rollout");
             std::swap(a, b);
         }
-        for (int32_t t = k; t < kn; ++t) {
-            const int r = kbc::launch_step(c->L, fsrc(j - 1, nxt, t), sets[nxt][t], c->shape);
+        for (; f < kn; ++f) {
+            const int r = kbc::launch_step(c->L, fsrc(j - 1, nxt, f), sets[nxt][f], c->shape);
             if (r) return launch_result(r, "lbm_adjoint_rollout recompute");
         }
         if (!once) {

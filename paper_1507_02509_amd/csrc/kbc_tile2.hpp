@@ -86,17 +86,25 @@ __device__ __forceinline__ void panel_tile(int u, int ntx, int nty, int& tx, int
 // workgroup barrier).  SLAB: the rows beyond the slab's edges, -2, -1 and
 // ny, ny + 1, come from the halo buffers (SlabHalo) instead of wrapping;
 // extended rows past row ny (a ragged last tile) only feed output rows the
-// tile does not store, and load row ny instead.
-template <int FORM, int COLL, int VAR, int GM, int TH, bool NT, bool SLAB = false>
-__device__ __forceinline__ void step2_tile(const typename Form<FORM>::S* __restrict__ src,
-                                           typename Form<FORM>::S* __restrict__ dst, int nx, int ny,
-                                           int64_t pitch, int x0, int y0, const Coef<typename Form<FORM>::R>& K,
-                                           const SlabHalo<typename Form<FORM>::S>& halo = {}) {
+// tile does not store, and load row ny instead.  `win` is the workgroup's LDS
+// window of step2_values<TH>() values.  MID: the state after the first step is
+// written too, to `mid`.
+template <int TH>
+constexpr int step2_values() {
+    return 9 * TH * 66;
+}
+template <int FORM, int COLL, int VAR, int GM, int TH, bool NT, bool SLAB, bool MID>
+__device__ __forceinline__ void step2_in(typename Form<FORM>::S* __restrict__ winp,
+                                         const typename Form<FORM>::S* __restrict__ src,
+                                         typename Form<FORM>::S* __restrict__ mid,
+                                         typename Form<FORM>::S* __restrict__ dst, int nx, int ny, int64_t pitch,
+                                         int x0, int y0, const Coef<typename Form<FORM>::R>& K,
+                                         const SlabHalo<typename Form<FORM>::S>& halo) {
     using F = Form<FORM>;
     using R = typename F::R;
     using S = typename F::S;
     constexpr int TW = 64, EW = TW + 2, EH = TH + 2;
-    __shared__ S win[9][TH][EW];   // slot (row r, column c) holds output node (c - 1, r)
+    auto& win = *reinterpret_cast<S (*)[9][TH][EW]>(winp);   // slot (row r, column c) holds output node (c - 1, r)
 
     const int lane = static_cast<int>(threadIdx.x & 63u);
     const int w = __builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x >> 6));   // wave index
@@ -147,6 +155,14 @@ __device__ __forceinline__ void step2_tile(const typename Form<FORM>::S* __restr
             for (int i = 0; i < 9; ++i) {
                 const int r = ey - 1 + kCy[i];
                 if (r >= 0 && r < TH) win[i][r][lane + 1 + kCx[i]] = F::enc(g[i], i);
+            }
+            if constexpr (MID) {
+                const int y = y0 + ey - 1;
+                if (ey >= 1 && ey <= TH && y < ny && x0 + lane < nx) {
+                    const uint32_t o = static_cast<uint32_t>(x0 + lane) * sizeof(S);
+#pragma unroll
+                    for (int i = 0; i < 9; ++i) st_at<NT>(row_ptr(mid, y, i, pitch), o, F::enc(g[i], i));
+                }
             }
         };
         // steady state: both prefetches exist, so the wait before each row
@@ -223,6 +239,15 @@ __device__ __forceinline__ void step2_tile(const typename Form<FORM>::S* __restr
             for (int i = 0; i < 9; ++i) st_at<NT>(row_ptr(dst, y, i, pitch), c0, F::enc(g[i], i));
         }
     }
+}
+
+template <int FORM, int COLL, int VAR, int GM, int TH, bool NT, bool SLAB = false>
+__device__ __forceinline__ void step2_tile(const typename Form<FORM>::S* __restrict__ src,
+                                           typename Form<FORM>::S* __restrict__ dst, int nx, int ny,
+                                           int64_t pitch, int x0, int y0, const Coef<typename Form<FORM>::R>& K,
+                                           const SlabHalo<typename Form<FORM>::S>& halo = {}) {
+    __shared__ typename Form<FORM>::S win[step2_values<TH>()];
+    step2_in<FORM, COLL, VAR, GM, TH, NT, SLAB, false>(win, src, nullptr, dst, nx, ny, pitch, x0, y0, K, halo);
 }
 
 }  // namespace kbc
