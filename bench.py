@@ -5,21 +5,22 @@ Workload (the roofline run): one periodic 16384 x 16384 lattice, a seeded
 divergence-free random initial field with E(k) ~ k^4 exp(-2 (k/32)^2),
 u_rms = 0.05, rho = 1, nu = 1e-4, Grad initialisation with central
 differences; KBC model B, populations stored as FP32 deviations, FP32
-arithmetic.  The library's default launch runs two fused pull-stream +
-collide steps per kernel launch (the first step's result stays in LDS), so
-the state crosses HBM once per two steps.
+arithmetic.  The library's default launch runs four fused pull-stream +
+collide steps per kernel launch (the results of the first three stay in LDS),
+so the state crosses HBM once per four steps.
 
     python bench.py [--gpus 1] [--steps K] [--warmup W]
 
 prints one JSON line.  `value` is lattice updates per second (MLUPS) over the
-K timed steps.  `roofline` describes the dominant kernel: with two fused
+K timed steps.  `roofline` describes the dominant kernel: with several fused
 steps per launch it is bound by vector-ALU issue, so `bound` is "alu" and
 `achieved` counts the FP32 operations of its compiled collision against the
 published FP32 vector peak; the same object gives the HBM side per launch
 (72 B per node per launch over the launch time, against 8 TB/s).  With
---fusion 1 (one step per launch) the kernel is HBM-bound and `bound` is
-"hbm".  `cpu_baseline` times the FP64 CPU oracle on a bounded sample of the
-same workload on all host cores (up to 16) and on one core.
+--fusion 2,8 every launch runs two steps on 8-row tiles; with --fusion 1 (one
+step per launch) the kernel is HBM-bound and `bound` is "hbm".
+`cpu_baseline` times the FP64 CPU oracle on a bounded sample of the same
+workload on all host cores (up to 16) and on one core.
 """
 from __future__ import annotations
 
@@ -42,15 +43,17 @@ BYTES_PER_NODE = {"f16": 36, "f32": 72, "f64": 144}
 TRAFFIC_FILE = os.path.join(ROOT, "profiles", "step_traffic.json")
 _CSRC = os.path.join(ROOT, "paper_1507_02509_amd", "csrc")
 STEP_SOURCES = [os.path.join(_CSRC, f)
-                for f in ("kbc_step.hip", "kbc_step2.hip", "kbc_tile.hpp", "kbc_tile2.hpp", "kbc_device.hpp")]
+                for f in ("kbc_step.hip", "kbc_step2.hip", "kbc_step4.hip", "kbc_tile.hpp", "kbc_tile2.hpp",
+                          "kbc_tilen.hpp", "kbc_device.hpp")]
 # Floating-point operations of one KBC-B collision per node as compiled for
 # gfx950 (adds, multiplies, reciprocals and conversions count one, FMAs two),
-# counted in the single-step kernel's code: "compiled-instruction FLOPs", not
-# a minimal operation count of the method.  The vector peaks are MI355X's
+# counted in the single-step kernel's code without the guard's rarely entered
+# <ds|ds> branch (28): "compiled-instruction FLOPs", not a minimal operation
+# count of the method.  The vector peaks are MI355X's
 # published ones; the FP32 one assumes packed FP32 (two lanes per
 # instruction), which this library never issues, so at most half of it is
 # attainable here.
-FLOPS_PER_NODE_STEP = {"f32": 266, "f16": 302, "f64": 382}
+FLOPS_PER_NODE_STEP = {"f32": 224, "f16": 260, "f64": 312}
 VECTOR_PEAK_TFLOPS = {"f32": 157.3, "f16": 157.3, "f64": 78.6}
 VALU_ISSUE_PEAK = 256 * 64 * 2.4e9   # lane-instructions/s: 256 CUs, 64 lanes, nominal clock
 # untimed steps before each extra measurement, so that none is timed while the
@@ -102,6 +105,21 @@ def time_steps(sim, steps: int, warmup: int):
     torch.cuda.synchronize()
     wall = time.perf_counter() - wall0
     return t0.elapsed_time(t1) / steps, wall
+
+
+def steps_per_launch(sim, n, form, collision="kbc", exact=False, chosen=False):
+    """Fused steps per launch of a long lbm_step on an n x n lattice.  With the
+    default fused tile that is four where the lattice has at most one tall tile
+    per CU, and elsewhere unless arithmetic binds two already (the exact
+    stabiliser; FP16 KBC inside the 256 MiB last-level cache); an explicitly
+    chosen launch (chosen) is taken to differ from the default."""
+    if sim.fusion != 2 or chosen:
+        return sim.fusion
+    tall = 16 if form == "f64" else 28
+    if -(-n // 64) * -(-n // tall) <= 256:
+        return 4
+    cached = BYTES_PER_NODE[form] * n * n <= 256 * 2 ** 20
+    return 2 if collision == "kbc" and (exact or (form == "f16" and cached)) else 4
 
 
 def make_sim(n, form, collision, variant, nu, seed, k0, device):
@@ -243,7 +261,7 @@ def time_slab(dev, steps=200, slabs=8):
 def time_ensemble(dev, steps=60, persistent_steps=2000):
     """The uneven ensemble: 256 members, N in {128, 256, 512, 1024}, KBC-B FP32.
     (a) the library's default launch (one batched launch over all members'
-    tiles per two fused steps), `steps` steps; (b) the workload as stated:
+    tiles per four fused steps), `steps` steps; (b) the workload as stated:
     `persistent_steps` steps in ONE persistent launch (grid barrier between
     pairs of steps) with the launch configuration the autotuner picks for the
     persistent mode on this ensemble (timed on the ensemble itself, state
@@ -263,11 +281,11 @@ def time_ensemble(dev, steps=60, persistent_steps=2000):
     e1.record()
     torch.cuda.synchronize()
     ms = e0.elapsed_time(e1) / steps
-    spl = ens.fusion
+    spl = 4 if ens.fusion == 2 else ens.fusion      # 91 M nodes: beyond the last-level cache
     res = {"members": 256, "nodes": nodes, "ms_per_step": round(ms, 4),
            "mlups": round(nodes / (ms * 1e-3) / 1e6, 1), "steps_per_launch": spl,
            "hbm_frac": round(72 * nodes / (spl * ms * 1e-3) / 1e9 / HBM_PEAK_GBS, 4),
-           "launch": "one batched launch over all members per " + ("two steps" if spl == 2 else "step")}
+           "launch": "one batched launch over all members per " + ("four steps" if spl == 4 else "step")}
     best, _ = autotune.tune_ensemble(ens, steps=10, reps=2, persistent=True, use_cache=False)
     blocks = ens.blocks
     ens.step(2, persistent=True)
@@ -372,8 +390,8 @@ def main():
     ap.add_argument("--no-extras", action="store_true")
     ap.add_argument("--extras", default="forms,lbgk,exact,copy,adjoint,rollout,ensemble,slab,accuracy",
                     help="comma-separated extra measurements")
-    ap.add_argument("--extra-steps", type=int, default=50,
-                    help="timed steps for the other forms and the LBGK baseline")
+    ap.add_argument("--extra-steps", type=int, default=48,
+                    help="timed steps for the other forms and the LBGK baseline (48: whole launches of four)")
     args = ap.parse_args()
     if args.gpus != 1:
         print(json.dumps({"error": "this benchmark runs on one GPU; --gpus must be 1",
@@ -390,10 +408,12 @@ def main():
 
     progress(f"init {n}x{n} {args.form} KBC-{args.variant}")
     sim = make_sim(n, args.form, "kbc", args.variant, nu, seed, k0, dev)
+    # an explicit fusion with the default rows is the default launch
+    rows0 = sim.fusion_rows
     if args.fusion is not None:
         sim.set_fusion(*args.fusion)
-    spl = sim.fusion
     rows = sim.fusion_rows
+    spl = steps_per_launch(sim, n, args.form, chosen=rows != rows0)
     d0 = sim.diagnostics()
     ms, wall = time_steps(sim, args.steps, args.warmup)
     progress(f"timed {args.steps} steps: {ms:.4f} ms/step")
@@ -402,15 +422,16 @@ def main():
     torch.cuda.empty_cache()
     nodes = n * n
     mlups = nodes / (ms * 1e-3) / 1e6
-    launch_ms = ms * spl      # one launch advances spl steps (an odd step count adds one single step)
+    launch_ms = ms * spl      # one launch advances spl steps (the default 200 steps are whole launches)
     bytes_launch = BYTES_PER_NODE[args.form] * nodes      # state read + written once per launch
     hbm_gbs = bytes_launch / (launch_ms * 1e-3) / 1e9
-    key = f"{args.form}_kbc{args.variant}_{n}" + ("_fused2" if spl == 2 else "")
+    key = f"{args.form}_kbc{args.variant}_{n}" + (f"_fused{spl}" if spl > 1 else "")
     traffic = measured_traffic(key)
-    kname = (f"k_step2<{args.form},KBC-{args.variant},64x{rows}>" if spl == 2
-             else f"k_step<{args.form},KBC-{args.variant}>")
-    if spl == 2 and args.variant == "B":
-        # two steps per pass through HBM: the kernel is bound by vector
+    kname = {1: f"k_step<{args.form},KBC-{args.variant}>",
+             2: f"k_step2<{args.form},KBC-{args.variant},64x{rows}>",
+             4: f"k_step4<{args.form},KBC-{args.variant}>"}[spl]
+    if spl > 1 and args.variant == "B":
+        # several steps per pass through HBM: the kernel is bound by vector
         # arithmetic, not by HBM
         flops_launch = FLOPS_PER_NODE_STEP[args.form] * nodes * spl
         achieved = flops_launch / (launch_ms * 1e-3) / 1e12
@@ -447,7 +468,7 @@ def main():
             if form == args.form or "forms" not in want:
                 continue
             s = make_sim(n, form, "kbc", args.variant, nu, seed, k0, dev)
-            fs = s.fusion
+            fs = steps_per_launch(s, n, form)
             m, _ = time_steps(s, args.extra_steps, EXTRA_WARMUP)
             progress(f"{form}: {m:.4f} ms/step")
             del s
@@ -457,14 +478,14 @@ def main():
                 "mlups": round(nodes / (m * 1e-3) / 1e6, 1), "ms_per_step": round(m, 4), "steps_per_launch": fs,
                 "hbm_frac": round(BYTES_PER_NODE[form] * nodes / (fs * m * 1e-3) / 1e9 / HBM_PEAK_GBS, 4)}
     if "exact" in want:
-        # the exact stabiliser: per-node Newton root of the entropy condition
+        # the exact stabiliser: per-node root of the entropy condition
         from paper_1507_02509_amd import inputs
         from paper_1507_02509_amd.sim import Sim, beta_from_nu
         ux, uy = inputs.spectral(n, k0, 0.05, seed=seed, device=dev)
         s = Sim(n, n, beta_from_nu(nu), collision="kbc", variant=args.variant, form=args.form,
                 gamma_mode="exact", device=dev).init(ux, uy)
         del ux, uy
-        fs = s.fusion
+        fs = steps_per_launch(s, n, args.form, exact=True)
         m, _ = time_steps(s, args.extra_steps, EXTRA_WARMUP)
         progress(f"exact stabiliser: {m:.4f} ms/step")
         d = s.diagnostics()
@@ -475,7 +496,7 @@ def main():
             "over_estimate_time": round(m / ms, 3), "gamma_mean": d["gamma"]}
     if "lbgk" in want:
         s = make_sim(n, args.form, "lbgk", "A", nu, seed, k0, dev)
-        fs = s.fusion
+        fs = steps_per_launch(s, n, args.form, collision="lbgk")
         m, _ = time_steps(s, args.extra_steps, EXTRA_WARMUP)
         del s
         torch.cuda.empty_cache()

@@ -124,14 +124,15 @@ typedef struct {
  * offset within a population row is a 32-bit value.  A kernel launch holds at
  * most 2^32 - 1 work-items (the grid size of a dispatch is 32-bit); a call
  * whose launch would need more returns LBM_EUNSUPPORTED without making that
- * launch (every launch of lbm_step has the same grid, so it enqueues
- * nothing; lbm_adjoint_rollout may have enqueued earlier, smaller ones).
+ * launch (earlier launches of the same call may have been enqueued).
  * Work-items per node: 1 / rows-per-thread for the single step (1/4 with the
  * FP16 default 256 x 4 tile, 1 with the FP32 and FP64 defaults), 4 / rows for
- * the fused step (1/4 with 16-row tiles, 1/2 with FP64's 8), 1 / (rows per
+ * two fused steps (1/4 with 16-row tiles, 1/2 with FP64's 8), 1/4 to 1 for four
+ * (whose launch is not chosen where it would not fit), 1 / (rows per
  * thread) for the adjoint step (1/2 for FP32 and FP16 lattices of at least
- * 8192 tiles of 128 x 4 nodes, else 1), plus 1 for the forward step that
- * lbm_adjoint_rollout combines with it, and 1 for lbm_adjoint_init.  So every
+ * 8192 tiles of 128 x 4 nodes, else 1), 1/4 or 1/2 for two adjoint steps, as
+ * much again for the forward steps that lbm_adjoint_rollout combines with
+ * them, and 1 for lbm_adjoint_init.  So every
  * lattice whose buffers fit the device's memory steps in the default
  * configuration (the largest: about 2^32 nodes in FP16, two 77 GB population
  * buffers).  Offsets of rows within buffers are 64-bit everywhere. */
@@ -387,9 +388,9 @@ int lbm_adjoint_segment(lbm_ctx* c, const void* state0, void* const* slots, int3
  * buffers of this context's layout).  Segments run from last to first, their
  * states f^{s+1} .. f^{s+k-1} held in one of two slot sets (slots_a, slots_b:
  * seglen - 1 distinct buffers each, alternating between segments).  Each
- * launch runs one adjoint step of segment j and, in the same grid, one
- * forward step recomputing a state of segment j - 1 into the other set, so
- * the recomputation costs no launches of its own and the two fill the chip
+ * launch runs two adjoint steps of segment j (one for the exact stabiliser and
+ * an odd remainder) and, in the same grid, as many forward steps recomputing
+ * states of segment j - 1 into the other set, so the recomputation costs no launches of its own and the two fill the chip
  * together on small lattices.  The result is bitwise that of calling
  * lbm_adjoint_segment for every segment in turn.  lam_in holds dL/df^{nsteps}
  * on entry; *which receives 0 if dL/df^0 ended in lam_in, 1 if in lam_out;

@@ -2,7 +2,8 @@
 //
 // A context borrows the caller's two population buffers and records the
 // lattice parameters, the step counter and the buffer that holds the current
-// state.  Its only allocations are the scratch arrays of lbm_diagnostics.
+// state.  What it allocates is scratch: the partial sums of lbm_diagnostics and
+// of the adjoint, and the transforms of lbm_spectra.
 #include <math.h>
 #include <stdarg.h>
 #include <stdio.h>
@@ -743,11 +744,18 @@ int lbm_adjoint_rollout(lbm_ctx* c, const void* const* ckpts, int32_t nsteps, in
     // The steps' dL/dbeta slices are summed once at the end where all of them
     // take at most 64 MiB (two launches a pass instead of two a segment), else
     // segment by segment; the order of the additions is the same.
-    const bool once = ng * nsteps <= (int64_t{8} << 20);
-    const int64_t kr = (static_cast<int64_t>(once ? nsteps : seglen) + 63) / 64 * 64;
+    bool once = ng * nsteps <= (int64_t{8} << 20);
+    int64_t kr = (static_cast<int64_t>(once ? nsteps : seglen) + 63) / 64 * 64;
     // room for lbm_adjoint_init too, which usually follows: growing the scratch
-    // then would synchronise (0.2 ms in the middle of a backward pass)
+    // then would synchronise (0.2 ms in the middle of a backward pass).  On a
+    // full device the segments' own room is enough.
     int rc = ensure_ascratch(c, std::max(static_cast<size_t>(nb + ng * kr + kr), init_scratch(c)));
+    if (rc == LBM_ENOMEM) {
+        (void)hipGetLastError();
+        once = false;
+        kr = (static_cast<int64_t>(seglen) + 63) / 64 * 64;
+        rc = ensure_ascratch(c, static_cast<size_t>(nb + ng * kr + kr));
+    }
     if (rc) return rc;
     double* const slices = c->ascratch + nb;
     double* const totals = slices + ng * kr;

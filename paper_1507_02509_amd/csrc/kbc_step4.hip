@@ -96,7 +96,11 @@ int step4_shape(const Lattice& L, const int32_t* sizes, int count, double state_
             n += static_cast<int64_t>((sizes[2 * k] + 63) / 64) * ((sizes[2 * k + 1] + rows - 1) / rows);
         return n;
     };
-    auto shape = [](int rows, int waves, bool store_nt = true) { return step4_code(rows, waves, store_nt); };
+    // a very wide, flat lattice can need more work-items than a dispatch holds
+    // where tiles of two steps (four waves) do not: 2^28 x 25 FP16 LBGK
+    auto shape = [&](int rows, int waves, bool store_nt = true) {
+        return grid_fits(8 * ((tiles(rows) + 7) / 8), 64 * waves) ? step4_code(rows, waves, store_nt) : 0;
+    };
     // one tile per CU (an ensemble's launches are built for many).  Two rows only up to half of that: a tile's six margin
     // rows weigh most there (192^2 with 288 such tiles 1.82, with four rows
     // 1.44).  FP64 has room for fewer waves' registers, and not for 28 rows.
