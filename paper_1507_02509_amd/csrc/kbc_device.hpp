@@ -52,9 +52,6 @@ template <> struct Form<F16> {
     __device__ static __forceinline__ R dec(S v, int i) {
         return __builtin_fmaf(static_cast<float>(v), 1.0f / static_cast<float>(1 << f16_shift(i)), 0.0f);
     }
-    __device__ static __forceinline__ S enc(R v, int i) {
-        return static_cast<_Float16>(v * static_cast<float>(1 << f16_shift(i)));
-    }
     __device__ static __forceinline__ double dec64(S v, int i) {
         return static_cast<double>(static_cast<float>(v)) / static_cast<double>(1 << f16_shift(i));
     }
@@ -70,7 +67,6 @@ template <> struct Form<F32> {
     using R = float;
     static constexpr int bytes = 4;
     __device__ static __forceinline__ R dec(S v, int) { return v; }
-    __device__ static __forceinline__ S enc(R v, int) { return v; }
     __device__ static __forceinline__ double dec64(S v, int) { return static_cast<double>(v); }
     __device__ static __forceinline__ S enc64(double v, int) { return static_cast<float>(v); }
 };
@@ -80,7 +76,6 @@ template <> struct Form<F64> {
     using R = double;
     static constexpr int bytes = 8;
     __device__ static __forceinline__ R dec(S v, int) { return v; }
-    __device__ static __forceinline__ S enc(R v, int) { return v; }
     __device__ static __forceinline__ double dec64(S v, int) { return v; }
     __device__ static __forceinline__ S enc64(double v, int) { return v; }
 };
@@ -163,23 +158,41 @@ template <typename R> constexpr R guard_bound() { return R(1300); }
 // FP32 KBC-B takes 151 vector instructions per collision (181 with unscaled
 // populations spread one by one and <ds|ds> always formed).  The fused step of
 // an FP16 lattice, bound by instruction issue, went from 35.1 to 31.8 us per
-// pair of steps at 1921 x 1083, of FP64 2-3 %; FP32 at 8192^2 from 975 to 918,
-// where it now moves 5.3 TB/s and is bound by memory as much.
+// pair of steps at 1921 x 1083 with it, of FP64 2-3 %; FP32 at 8192^2 from 975
+// to 918, where it moves 5.3 TB/s and is bound by memory as much.
 // The natural-moment variants (C, D) sum in the order that has been checked
 // over 2000-step gradients: there too every scale is a power of two.
-template <typename R, int VAR, int GM>
-__device__ __forceinline__ void kbc_forward(const R (&g)[9], const Coef<R>& K, KbcNode<R>& n) {
+//
+// The populations come as sums and differences of opposite ones (PopSums).
+// They may be given in units of their own: U times the axis populations and
+// U Q times the diagonal ones (powers of two; U = Q = 1 for plain values).  All
+// of n is then in units of U (every moment is homogeneous in the deviations
+// and rho0, and velocities, weights, gamma and the guard have no unit), with
+// the factors 1 / Q in multiplications that are there anyway.
+template <typename R> struct PopSums {
+    R s13, s24, s57, s68;               // g1 + g3, ...
+    R d13, d24, d57, d68;               // g1 - g3, ...
+};
+template <typename R>
+__device__ __forceinline__ PopSums<R> pop_sums(const R (&g)[9]) {
+    return {g[1] + g[3], g[2] + g[4], g[5] + g[7], g[6] + g[8], g[1] - g[3], g[2] - g[4], g[5] - g[7], g[6] - g[8]};
+}
+template <typename R, int VAR, int GM, int U, int Q, typename Rest>
+__device__ __forceinline__ void kbc_forward_sums(const PopSums<R>& p, Rest add_rest, const Coef<R>& K,
+                                                 KbcNode<R>& n) {
     constexpr bool kCentral = (VAR == VA || VAR == VB);   // s in the co-moving frame, eq. (cm)
     constexpr bool kTrace = (VAR == VA || VAR == VC);     // T belongs to s
+    constexpr R q = R(1) / R(Q);
+    auto plus = [](R a, R b) { return Q == 1 ? a + b : fmaR(q, b, a); };   // a + q b
     // conserved moments, eq. (moments) restricted to the deviations
-    const R s13 = g[1] + g[3], s24 = g[2] + g[4], s57 = g[5] + g[7], s68 = g[6] + g[8];
-    const R d13 = g[1] - g[3], d24 = g[2] - g[4], d57 = g[5] - g[7], d68 = g[6] - g[8];
+    const R s13 = p.s13, s24 = p.s24, s57 = p.s57, s68 = p.s68;
+    const R d13 = p.d13, d24 = p.d24;
     const R sd = s57 + s68, sa = s13 + s24;
-    const R dr = (g[0] + sd) + sa;                 // rho - rho0
-    const R mq = d57 - d68, pq = d57 + d68;
-    const R jx = d13 + mq;                         // rho u_x
-    const R jy = d24 + pq;                         // rho u_y
-    const R rho = K.rho0 + dr;
+    const R dr = plus(sa, add_rest(sd));           // rho - rho0
+    const R mq = p.d57 - p.d68, pq = p.d57 + p.d68;
+    const R jx = plus(d13, mq);                    // rho u_x
+    const R jy = plus(d24, pq);                    // rho u_y
+    const R rho = U == 1 ? K.rho0 + dr : fmaR(R(U), K.rho0, dr);
     const R ir = rcpR(rho);
     const R ux = jx * ir, uy = jy * ir;
     const R uxx = ux * ux, uyy = uy * uy;
@@ -191,12 +204,13 @@ __device__ __forceinline__ void kbc_forward(const R (&g)[9], const Coef<R>& K, K
     const R juy = jy * uy;
     const R jsum = fmaR(jx, ux, juy);          // rho |u|^2
     const R jdif = fmaR(jx, ux, -juy);         // rho (u_x^2 - u_y^2)
-    const R dT = fmaR(R(2), sd, sa) - fmaR(R(2.0 / 3.0), dr, jsum);
+    const R dT = fmaR(R(2) * q, sd, sa) - fmaR(R(2.0 / 3.0), dr, jsum);
     const R dN = (s13 - s24) - jdif;
-    const R dP = fmaR(-jx, uy, s57 - s68);
-    const R dQx = fmaR(R(-1.0 / 3.0), jx, mq);
-    const R dQy = fmaR(R(-1.0 / 3.0), jy, pq);
-    const R dA = fmaR(R(-1.0 / 3.0), jsum, fmaR(R(-1.0 / 9.0), dr, sd));
+    const R dP = fmaR(-jx, uy, Q == 1 ? s57 - s68 : q * (s57 - s68));
+    const R dQx = fmaR(R(-Q / 3.0), jx, mq);       // Q times dQ_xyy, dQ_yxx and dA
+    const R dQy = fmaR(R(-Q / 3.0), jy, pq);
+    const R dA = fmaR(R(-Q / 3.0), jsum, fmaR(R(-Q / 9.0), dr, sd));
+    constexpr R hq = R(0.5) * q;
     n.dT = dT; n.dN = dN; n.dP = dP;
 
     // Shear part s, Table kbc_moment_grouping, from (T_s +- N) / 4, Q_xyy,s / 2
@@ -242,9 +256,9 @@ __device__ __forceinline__ void kbc_forward(const R (&g)[9], const Coef<R>& K, K
     // higher-order part h = df - s: moments (T - T_s, 0, 0, dQ - Q_s, dA - A_s)
     R (&dh)[9] = n.dh;
     {
-        const R xh = kCentral ? fmaR(R(0.5), dQx, -ox) : R(0.5) * dQx;
-        const R yh = kCentral ? fmaR(R(0.5), dQy, -oy) : R(0.5) * dQy;
-        const R ah = kCentral ? fmaR(R(0.5), dA, -a2) : R(0.5) * dA;
+        const R xh = kCentral ? fmaR(hq, dQx, -ox) : hq * dQx;
+        const R yh = kCentral ? fmaR(hq, dQy, -oy) : hq * dQy;
+        const R ah = kCentral ? fmaR(hq, dA, -a2) : hq * dA;
         dh[0] = kTrace ? ah : fmaR(R(-0.5), dT, ah);
         if constexpr (kCentral) {
             const R eh = kTrace ? -ah : tq - ah;
@@ -330,6 +344,12 @@ __device__ __forceinline__ void kbc_forward(const R (&g)[9], const Coef<R>& K, K
         }
         n.gam = n.active ? gs : R(2);
     }
+}
+
+// The node's quantities from its deviations g.
+template <typename R, int VAR, int GM>
+__device__ __forceinline__ void kbc_forward(const R (&g)[9], const Coef<R>& K, KbcNode<R>& n) {
+    kbc_forward_sums<R, VAR, GM, 1, 1>(pop_sums(g), [&](R sd) { return g[0] + sd; }, K, n);
 }
 
 // Root of the entropy-maximum condition eq. (result1) in gamma,
@@ -472,15 +492,19 @@ __device__ __forceinline__ void unscaled(const KbcNode<R>& n, R (&ds)[9], R (&dh
     }
 }
 
-// One collision on the deviations g (in place).  Returns the gamma used.
-template <typename R, int COLL, int VAR, int GM>
-__device__ __forceinline__ R collide(R (&g)[9], const Coef<R>& K) {
+// One collision on a node's values (in place): U and Q are the units of the
+// axis and diagonal ones (see PopSums) and Z that of the rest population, 1 / Z
+// of the axis unit.  Returns the gamma used.
+template <typename R, int COLL, int VAR, int GM, int U, int Q, int Z>
+__device__ __forceinline__ R collide_units(R (&g)[9], const Coef<R>& K) {
+    constexpr R rz = R(1) / R(Z);
+    auto add_rest = [&](R sd) { return Q * Z == 1 ? g[0] + sd : fmaR(R(Q * Z), g[0], sd); };
+    const PopSums<R> p = pop_sums(g);
     if constexpr (COLL == LBGK) {
-        const R s13 = g[1] + g[3], s24 = g[2] + g[4], s57 = g[5] + g[7], s68 = g[6] + g[8];
-        const R d13 = g[1] - g[3], d24 = g[2] - g[4], d57 = g[5] - g[7], d68 = g[6] - g[8];
-        const R dr = (g[0] + (s57 + s68)) + (s13 + s24);
-        const R jx = d13 + (d57 - d68), jy = d24 + (d57 + d68);
-        const R rho = K.rho0 + dr;
+        auto plus = [](R a, R b) { return Q == 1 ? a + b : fmaR(R(1) / R(Q), b, a); };
+        const R dr = plus(p.s13 + p.s24, add_rest(p.s57 + p.s68));
+        const R jx = plus(p.d13, p.d57 - p.d68), jy = plus(p.d24, p.d57 + p.d68);
+        const R rho = U == 1 ? K.rho0 + dr : fmaR(R(U), K.rho0, dr);
         const R ir = rcpR(rho);
         const R ux = jx * ir, uy = jy * ir;
         const R uxx = ux * ux, uyy = uy * uy, u2 = uxx + uyy;
@@ -503,7 +527,7 @@ __device__ __forceinline__ R collide(R (&g)[9], const Coef<R>& K) {
         e[8] = fmaR(R(3), umv, b6);
         e[6] = fmaR(R(-3), umv, b6);
         const R tb = R(2) * K.beta, omt = R(1) - tb;
-        const R tw[3] = {tb * R(weight(0)), tb * R(weight(1)), tb * R(weight(5))};
+        const R tw[3] = {tb * (R(weight(0)) * rz), tb * R(weight(1)), tb * (R(weight(5)) * R(Q))};
 #pragma unroll
         for (int i = 0; i < 9; ++i) {
             const R twi = tw[i == 0 ? 0 : (i < 5 ? 1 : 2)];
@@ -512,14 +536,14 @@ __device__ __forceinline__ R collide(R (&g)[9], const Coef<R>& K) {
         return R(2);
     } else {
         KbcNode<R> n;
-        kbc_forward<R, VAR, (GM == GEXACT ? GEST : GM)>(g, K, n);
+        kbc_forward_sums<R, VAR, (GM == GEXACT ? GEST : GM), U, Q>(p, add_rest, K, n);
         R gam = n.gam;
         if constexpr (GM == GEXACT) {
             if (n.active) gam = exact_gamma<R>(n, K);
         }
         // f' = f - beta (2 ds + gamma dh), eqs. (Egeneral), (ksh-mirror)
-        const R tb[3] = {R(4) * K.beta, R(2) * K.beta, K.beta};
-        const R bg[3] = {(R(2) * K.beta) * gam, K.beta * gam, (R(0.5) * K.beta) * gam};
+        const R tb[3] = {(R(4) * rz) * K.beta, R(2) * K.beta, R(Q) * K.beta};
+        const R bg[3] = {((R(2) * rz) * K.beta) * gam, K.beta * gam, ((R(0.5) * R(Q)) * K.beta) * gam};
 #pragma unroll
         for (int i = 0; i < 9; ++i) {
             const int k = i == 0 ? 0 : (i < 5 ? 1 : 2);
@@ -528,6 +552,43 @@ __device__ __forceinline__ R collide(R (&g)[9], const Coef<R>& K) {
             g[i] = fmaR(-bg[k], n.dh[i], t);
         }
         return gam;
+    }
+}
+
+// One collision on the deviations g (in place).  Returns the gamma used.
+template <typename R, int COLL, int VAR, int GM>
+__device__ __forceinline__ R collide(R (&g)[9], const Coef<R>& K) {
+    return collide_units<R, COLL, VAR, GM, 1, 1, 1>(g, K);
+}
+
+// One collision on a node's values in the storage form (in place).
+//
+// FP16 works in the units the values are stored in (2^s_i g_i), so that a value
+// is converted to binary32 and back and never scaled.  The conversions are kept
+// apart from the arithmetic: folded into it as mixed-precision FMAs they are
+// fewer instructions but slower ones (cycles per wave instruction among FP32
+// FMAs, six waves per SIMD: v_cvt_f32_f16 and v_cvt_f16_f32 2.3, v_fma_f32 2.5,
+// v_fma_mix_f32 4.5, v_fma_mixlo_f16 10.5, as much as a reciprocal).  KBC-B with
+// mixed FMAs / conversions, us per launch: two steps at 1921 x 1083 34.0 / 31.2,
+// four at 4096^2 409 / 382 (tiles of 32 rows).
+template <int FORM, int COLL, int VAR, int GM>
+__device__ __forceinline__ void collide_stored(typename Form<FORM>::S (&v)[9], const Coef<typename Form<FORM>::R>& K) {
+    if constexpr (FORM == F16) {
+        constexpr int sa = f16_shift(1);
+        float g[9];
+#pragma unroll
+        for (int i = 0; i < 9; ++i) {
+            g[i] = static_cast<float>(v[i]);
+            asm("" : "+v"(g[i]));
+        }
+        collide_units<float, COLL, VAR, GM, 1 << sa, 1 << (f16_shift(5) - sa), 1 << (sa - f16_shift(0))>(g, K);
+#pragma unroll
+        for (int i = 0; i < 9; ++i) {
+            asm("" : "+v"(g[i]));
+            v[i] = static_cast<_Float16>(g[i]);
+        }
+    } else {
+        collide<typename Form<FORM>::R, COLL, VAR, GM>(v, K);
     }
 }
 

@@ -19,10 +19,10 @@
 //     collisions in the margins.  FP32 LBGK 4096^2 117 / 68, FP64 LBGK 2048^2
 //     58.2 / 37.3, FP16 LBGK 3072^2 44.6 / 38.0; FP32 KBC-B 8192^2 477 / 391,
 //     4096^2 122 / 98, 1280^2 13.8 / 12.4, 1024^2 9.1 / 9.1; FP64 KBC-B 3072^2 138 /
-//     127, 1024^2 15.7 / 15.7; FP16 KBC-B 4096^2 106 / 99.
+//     127, 1024^2 15.7 / 15.7; FP16 KBC-B 4096^2 97 / 93.
 //
 // Two steps stay where arithmetic binds: FP16 KBC inside the last-level cache
-// (1536^2 17.4 / 17.9) and the exact stabiliser beyond one tile per CU (1024^2
+// (1536^2 16.1 / 16.2) and the exact stabiliser beyond one tile per CU (1024^2
 // 15.0 / 16.7).
 #include "kbc_launch.hpp"
 #include "kbc_tilen.hpp"
@@ -123,7 +123,8 @@ int step4_shape(const Lattice& L, const int32_t* sizes, int count, double state_
     if (f64) return L.collision == LBGK ? shape(12, 12, nt != 0) : shape(12, 8, !light || nt != 0);
     if (L.form == F16) {
         if (light) return shape(24, 8, nt != 0);
-        return state_bytes > 256.0 * 1024.0 * 1024.0 ? shape(32, 8) : 0;
+        // (40 rows 93, 32 rows 95, 24 rows 97 us per step at 4096^2)
+        return state_bytes > 256.0 * 1024.0 * 1024.0 ? shape(40, 12) : 0;
     }
     if (light && !nt) return shape(12, 8, false);
     // FP32: the height whose busiest CU has the least to do.  The order this

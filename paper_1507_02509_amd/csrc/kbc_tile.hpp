@@ -111,7 +111,6 @@ __device__ __forceinline__ void step_tile(const typename Form<FORM>::S* __restri
                                           const Coef<typename Form<FORM>::R>& K,
                                           const SlabHalo<typename Form<FORM>::S>& halo = {}) {
     using F = Form<FORM>;
-    using R = typename F::R;
     using S = typename F::S;
     constexpr int TW = 64 * TXW;            // tile width
     constexpr int WR = 4 / TXW;             // wave rows per tile
@@ -134,19 +133,19 @@ __device__ __forceinline__ void step_tile(const typename Form<FORM>::S* __restri
             else
                 return row_ptr(src, yy, i, pitch);
         };
-        R g[9];
-        g[0] = F::dec(ld_at(in(y, 0), c0), 0);
-        g[1] = F::dec(ld_at(in(y, 1), cm), 1);
-        g[2] = F::dec(ld_at(in(ym, 2), c0), 2);
-        g[3] = F::dec(ld_at(in(y, 3), cp), 3);
-        g[4] = F::dec(ld_at(in(yp, 4), c0), 4);
-        g[5] = F::dec(ld_at(in(ym, 5), cm), 5);
-        g[6] = F::dec(ld_at(in(ym, 6), cp), 6);
-        g[7] = F::dec(ld_at(in(yp, 7), cp), 7);
-        g[8] = F::dec(ld_at(in(yp, 8), cm), 8);
-        collide<R, COLL, VAR, GM>(g, K);
+        S v[9];
+        v[0] = ld_at(in(y, 0), c0);
+        v[1] = ld_at(in(y, 1), cm);
+        v[2] = ld_at(in(ym, 2), c0);
+        v[3] = ld_at(in(y, 3), cp);
+        v[4] = ld_at(in(yp, 4), c0);
+        v[5] = ld_at(in(ym, 5), cm);
+        v[6] = ld_at(in(ym, 6), cp);
+        v[7] = ld_at(in(yp, 7), cp);
+        v[8] = ld_at(in(yp, 8), cm);
+        collide_stored<FORM, COLL, VAR, GM>(v, K);
 #pragma unroll
-        for (int i = 0; i < 9; ++i) st_at<NT>(row_ptr(dst, y, i, pitch), c0, F::enc(g[i], i));
+        for (int i = 0; i < 9; ++i) st_at<NT>(row_ptr(dst, y, i, pitch), c0, v[i]);
     }
 }
 

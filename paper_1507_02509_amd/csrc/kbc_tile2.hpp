@@ -100,9 +100,7 @@ __device__ __forceinline__ void step2_in(typename Form<FORM>::S* __restrict__ wi
                                          typename Form<FORM>::S* __restrict__ dst, int nx, int ny, int64_t pitch,
                                          int x0, int y0, const Coef<typename Form<FORM>::R>& K,
                                          const SlabHalo<typename Form<FORM>::S>& halo) {
-    using F = Form<FORM>;
-    using R = typename F::R;
-    using S = typename F::S;
+    using S = typename Form<FORM>::S;
     constexpr int TW = 64, EW = TW + 2, EH = TH + 2;
     auto& win = *reinterpret_cast<S (*)[9][TH][EW]>(winp);   // slot (row r, column c) holds output node (c - 1, r)
 
@@ -145,23 +143,20 @@ __device__ __forceinline__ void step2_in(typename Form<FORM>::S* __restrict__ wi
             v[7] = ld_at(in(yp, 7), cp);
             v[8] = ld_at(in(yp, 8), cm);
         };
-        auto row = [&](int ey, const S (&v)[9]) {
-            R g[9];
-#pragma unroll
-            for (int i = 0; i < 9; ++i) g[i] = F::dec(v[i], i);
-            collide<R, COLL, VAR, GM>(g, K);
+        auto row = [&](int ey, S (&v)[9]) {
+            collide_stored<FORM, COLL, VAR, GM>(v, K);
             // node (lane, ey - 1) -> slot (lane + v_x + 1, ey - 1 + v_y); the row test is uniform
 #pragma unroll
             for (int i = 0; i < 9; ++i) {
                 const int r = ey - 1 + kCy[i];
-                if (r >= 0 && r < TH) win[i][r][lane + 1 + kCx[i]] = F::enc(g[i], i);
+                if (r >= 0 && r < TH) win[i][r][lane + 1 + kCx[i]] = v[i];
             }
             if constexpr (MID) {
                 const int y = y0 + ey - 1;
                 if (ey >= 1 && ey <= TH && y < ny && x0 + lane < nx) {
                     const uint32_t o = static_cast<uint32_t>(x0 + lane) * sizeof(S);
 #pragma unroll
-                    for (int i = 0; i < 9; ++i) st_at<NT>(row_ptr(mid, y, i, pitch), o, F::enc(g[i], i));
+                    for (int i = 0; i < 9; ++i) st_at<NT>(row_ptr(mid, y, i, pitch), o, v[i]);
                 }
             }
         };
@@ -193,7 +188,7 @@ __device__ __forceinline__ void step2_in(typename Form<FORM>::S* __restrict__ wi
             const int side = k / EH;
             const int ey = k - side * EH;
             const int gx = pmod(side ? x0 + TW : x0 - 1, nx);
-            R g[9];
+            S v[9];
             if constexpr (SLAB) {
                 const int y = y0 - 1 + ey < ny ? y0 - 1 + ey : ny;
 #pragma unroll
@@ -201,24 +196,24 @@ __device__ __forceinline__ void step2_in(typename Form<FORM>::S* __restrict__ wi
                     const int xs = wrap1(gx - kCx[i], nx), ys = y - kCy[i];
                     const S* b = ys < 0 ? halo.lo : (ys >= ny ? halo.hi : src);
                     const int r = ys < 0 ? ys + 2 : (ys >= ny ? ys - ny : ys);
-                    g[i] = F::dec(b[(static_cast<int64_t>(r) * 9 + i) * pitch + xs], i);
+                    v[i] = b[(static_cast<int64_t>(r) * 9 + i) * pitch + xs];
                 }
             } else {
                 const int y = pmod(y0 - 1 + ey, ny);
 #pragma unroll
                 for (int i = 0; i < 9; ++i) {
                     const int xs = wrap1(gx - kCx[i], nx), ys = wrap1(y - kCy[i], ny);
-                    g[i] = F::dec(src[(static_cast<int64_t>(ys) * 9 + i) * pitch + xs], i);
+                    v[i] = src[(static_cast<int64_t>(ys) * 9 + i) * pitch + xs];
                 }
             }
-            collide<R, COLL, VAR, GM>(g, K);
+            collide_stored<FORM, COLL, VAR, GM>(v, K);
             // node (-1 or 64, ey - 1): only the populations that move into
             // the tile land in a column the output nodes read
 #pragma unroll
             for (int i = 0; i < 9; ++i) {
                 if (kCx[i] != (side ? -1 : 1)) continue;
                 const int r = ey - 1 + kCy[i];
-                if (r >= 0 && r < TH) win[i][r][side ? EW - 2 : 1] = F::enc(g[i], i);
+                if (r >= 0 && r < TH) win[i][r][side ? EW - 2 : 1] = v[i];
             }
         }
     }
@@ -231,12 +226,12 @@ __device__ __forceinline__ void step2_in(typename Form<FORM>::S* __restrict__ wi
         const int y = y0 + oy;
         if (y >= ny) break;
         if (gx < nx) {
-            R g[9];
+            S v[9];
 #pragma unroll
-            for (int i = 0; i < 9; ++i) g[i] = F::dec(win[i][oy][lane + 1], i);
-            collide<R, COLL, VAR, GM>(g, K);
+            for (int i = 0; i < 9; ++i) v[i] = win[i][oy][lane + 1];
+            collide_stored<FORM, COLL, VAR, GM>(v, K);
 #pragma unroll
-            for (int i = 0; i < 9; ++i) st_at<NT>(row_ptr(dst, y, i, pitch), c0, F::enc(g[i], i));
+            for (int i = 0; i < 9; ++i) st_at<NT>(row_ptr(dst, y, i, pitch), c0, v[i]);
         }
     }
 }

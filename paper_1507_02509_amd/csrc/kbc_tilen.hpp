@@ -48,9 +48,7 @@ __device__ __forceinline__ void stepn_rest(typename Form<FORM>::S* __restrict__ 
                                            typename Form<FORM>::S* __restrict__ dst, int nx, int ny, int64_t pitch,
                                            int x0, int y0, int th, int lane, int w,
                                            const Coef<typename Form<FORM>::R>& K) {
-    using F = Form<FORM>;
-    using R = typename F::R;
-    using E = typename F::S;
+    using E = typename Form<FORM>::S;
     constexpr int M = T - 2;                              // window margin around the tile
     constexpr int WH = TH + 2 * M, WW = 64 + 2 * M;
     constexpr int H = T - S;                              // this step's margin
@@ -59,19 +57,19 @@ __device__ __forceinline__ void stepn_rest(typename Form<FORM>::S* __restrict__ 
     constexpr bool even = S % 2 == 0;
     __syncthreads();
     // the node at window offset o (row * WW + column)
-    auto node = [&](int o, R (&g)[9]) {
+    auto node = [&](int o, E (&v)[9]) {
         const E* p = win + o;
 #pragma unroll
         for (int i = 0; i < 9; ++i) {
             if constexpr (even)
-                g[i] = F::dec(p[i * WH * WW], i);
+                v[i] = p[i * WH * WW];
             else
-                g[i] = F::dec(p[opp(i) * WH * WW - kCy[i] * WW - kCx[i]], i);
+                v[i] = p[opp(i) * WH * WW - kCy[i] * WW - kCx[i]];
         }
-        collide<R, COLL, VAR, GM>(g, K);
+        collide_stored<FORM, COLL, VAR, GM>(v, K);
     };
     for (int t = w; t < packed + rows; t += NW) {
-        R g[9];
+        E v[9];
         if constexpr (S < T) {
             int o = (t - packed + M - H) * WW + lane + M;
             bool on = true;
@@ -82,21 +80,21 @@ __device__ __forceinline__ void stepn_rest(typename Form<FORM>::S* __restrict__ 
                 on = k < side;
             }
             if (on) {
-                node(o, g);
+                node(o, v);
                 E* p = win + o;
 #pragma unroll
                 for (int i = 0; i < 9; ++i) {
                     if constexpr (even)
-                        p[opp(i) * WH * WW] = F::enc(g[i], i);
+                        p[opp(i) * WH * WW] = v[i];
                     else
-                        p[i * WH * WW + kCy[i] * WW + kCx[i]] = F::enc(g[i], i);
+                        p[i * WH * WW + kCy[i] * WW + kCx[i]] = v[i];
                 }
             }
         } else if (x0 + lane < nx) {
-            node((t + M) * WW + lane + M, g);
+            node((t + M) * WW + lane + M, v);
             const uint32_t c0 = static_cast<uint32_t>(x0 + lane) * sizeof(E);
 #pragma unroll
-            for (int i = 0; i < 9; ++i) st_at<NT>(row_ptr(dst, y0 + t, i, pitch), c0, F::enc(g[i], i));
+            for (int i = 0; i < 9; ++i) st_at<NT>(row_ptr(dst, y0 + t, i, pitch), c0, v[i]);
         }
     }
     if constexpr (S < T)
@@ -109,9 +107,7 @@ template <int FORM, int COLL, int VAR, int GM, int T, int TH, int NW, bool NT>
 __device__ __forceinline__ void stepn_tile(const typename Form<FORM>::S* __restrict__ src,
                                            typename Form<FORM>::S* __restrict__ dst, int nx, int ny, int64_t pitch,
                                            int x0, int y0, const Coef<typename Form<FORM>::R>& K) {
-    using F = Form<FORM>;
-    using R = typename F::R;
-    using E = typename F::S;
+    using E = typename Form<FORM>::S;
     static_assert(T >= 3, "two steps have a tile of their own (step2_tile)");
     constexpr int M = T - 2, H = T - 1;
     constexpr int WH = TH + 2 * M, WW = 64 + 2 * M;
@@ -138,15 +134,12 @@ __device__ __forceinline__ void stepn_tile(const typename Form<FORM>::S* __restr
         v[7] = ld_at(row_ptr(src, yp, 7, pitch), cp);
         v[8] = ld_at(row_ptr(src, yp, 8, pitch), cm);
     };
-    auto row = [&](int r, const E (&v)[9]) {
-        R g[9];
-#pragma unroll
-        for (int i = 0; i < 9; ++i) g[i] = F::dec(v[i], i);
-        collide<R, COLL, VAR, GM>(g, K);
+    auto row = [&](int r, E (&v)[9]) {
+        collide_stored<FORM, COLL, VAR, GM>(v, K);
 #pragma unroll
         for (int i = 0; i < 9; ++i) {
             const int a = r - 1 + kCy[i];
-            if (a >= 0 && a < WH) win[(i * WH + a) * WW + lane + M + kCx[i]] = F::enc(g[i], i);
+            if (a >= 0 && a < WH) win[(i * WH + a) * WW + lane + M + kCx[i]] = v[i];
         }
     };
     // the wave's rows: the first one's loads are in flight during the packed
@@ -175,16 +168,13 @@ __device__ __forceinline__ void stepn_tile(const typename Form<FORM>::S* __restr
         v[6] = pm[6 * pitch + xp];
         v[7] = pp[7 * pitch + xp];
         v[8] = pp[8 * pitch + xm];
-        R g[9];
-#pragma unroll
-        for (int i = 0; i < 9; ++i) g[i] = F::dec(v[i], i);
-        collide<R, COLL, VAR, GM>(g, K);
+        collide_stored<FORM, COLL, VAR, GM>(v, K);
         // window column c - 1 (+ v_x), window row q - 1 (+ v_y): the outer
         // ring's outward populations have no slot
 #pragma unroll
         for (int i = 0; i < 9; ++i) {
             const int a = q - 1 + kCy[i], b = c - 1 + kCx[i];
-            if (a >= 0 && a < WH && b >= 0 && b < WW) win[(i * WH + a) * WW + b] = F::enc(g[i], i);
+            if (a >= 0 && a < WH && b >= 0 && b < WW) win[(i * WH + a) * WW + b] = v[i];
         }
     }
     for (; r + 2 * NW < rows; r += 2 * NW) {
@@ -230,7 +220,7 @@ int step4_many(int code, const Launch& l) {
         if (code == step4_code(24, 8, false)) return l.template at<24, 8, false>();
     }
     if constexpr (FORM == F16 && kEst)
-        if (code == step4_code(32, 8)) return l.template at<32, 8, true>();
+        if (code == step4_code(40, 12)) return l.template at<40, 12, true>();
     if constexpr (FORM == F64 && COLL == LBGK) {
         if (code == step4_code(12, 12)) return l.template at<12, 12, true>();
         if (code == step4_code(12, 12, false)) return l.template at<12, 12, false>();
