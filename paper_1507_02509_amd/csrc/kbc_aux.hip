@@ -176,26 +176,6 @@ __device__ __forceinline__ void block_store(double (&acc)[CNT], double* partials
     }
 }
 
-// ln(f / W) for f / W in [1/2, 2], from s = (f - W) / (f + W): 2 atanh(s) =
-// 2 s P(s^2), P the polynomial of degree 10 with the smallest largest relative
-// error on s^2 <= 1/9 (1.3e-18; coefficients by Remez's exchange algorithm).
-// 17 FP64 instructions, against about 100 for the library logarithm and 11 for
-// the division f / W; and as f - W is formed from the stored deviation, no
-// digits of a small deviation are lost.
-__device__ __forceinline__ double atanh_poly(double z) {
-    double p = 0.08504923007075064;
-    p = fmaR(z, p, 0.04172462195061191);
-    p = fmaR(z, p, 0.06052477641340325);
-    p = fmaR(z, p, 0.06650560071689546);
-    p = fmaR(z, p, 0.07693274239195039);
-    p = fmaR(z, p, 0.09090872237804135);
-    p = fmaR(z, p, 0.11111111976861492);
-    p = fmaR(z, p, 0.14285714274058622);
-    p = fmaR(z, p, 0.20000000000077559);
-    p = fmaR(z, p, 0.33333333333333154);
-    return fmaR(z, p, 1.0);
-}
-
 // u = j / r to within an ulp: one refined reciprocal of the density and a
 // correction step per component (11 instructions); the library division, 11
 // instructions each, where the density is too small or large for that (or not
@@ -276,7 +256,10 @@ __global__ __launch_bounds__(256) void k_diag(const typename Form<FORM>::S* __re
             sv[ey][lane + 2] = v;
             if (ey < 2 || ey >= TH + 2 || yy >= ny || x0 + lane >= nx) continue;
             const double u2 = u * u + v * v;
-            // entropy -sum f ln(f / W): the general form where a population is
+            // entropy -sum f ln(f / W), with ln(f / W) = 2 atanh of (f - W) / (f + W)
+            // (17 FP64 instructions, against about 100 for the library logarithm
+            // and 11 for the division f / W; and as f - W is formed from the
+            // stored deviation, no digits of a small one are lost): the general form where a population is
             // beyond a factor two of its weight (or not finite: then dr is not)
             double Sn = 0.0, zmax = 0.0;
 #pragma unroll

@@ -371,7 +371,11 @@ __device__ __forceinline__ void kbc_forward(const R (&g)[9], const Coef<R>& K, K
 // equilibrium, ln(1 + x) is its Taylor polynomial, of degree 6 or 10, by
 // Horner's rule: six or ten FMAs against the general form's logarithm,
 // reciprocal and guard (FP32) or the library log1p (FP64).  The truncation is
-// below 1.4e-10 and 8e-20 relative, the evaluation within 1.2e-7 and an ulp.  The
+// below 1.4e-10 and 8e-20 relative, the evaluation within 1.2e-7 and an ulp.
+// Above that and up to 1/2 the FP64 logarithm is log1p_mid; the library's (about
+// 100 instructions, nine times an iteration) is left to nodes beyond.  A few
+// such nodes set the time of their waves: 300 x 217 FP64 KBC-B 51 -> 18 us per
+// step, 1024^2 225 -> 90, the adjoint step of 1024^2 353 -> 133.  The
 // choice is the node's own (all nine of its arguments small), so a node's
 // result does not depend on which nodes share its wave; a wave skips the
 // general form when none of its nodes needs it.  The quantities that do not change
@@ -411,6 +415,29 @@ __device__ __forceinline__ double log1p_small(double x) {
     p = fmaR(x, p, 1.0);
     return x * p;
 }
+// atanh(s) = s P(s^2) for s^2 = z <= 1/9, i.e. logarithms 2 atanh(s) of
+// arguments in [1/2, 2]: P the polynomial of degree 10 with the smallest
+// largest relative error (1.3e-18; coefficients by Remez's exchange algorithm).
+__device__ __forceinline__ double atanh_poly(double z) {
+    double p = 0.08504923007075064;
+    p = fmaR(z, p, 0.04172462195061191);
+    p = fmaR(z, p, 0.06052477641340325);
+    p = fmaR(z, p, 0.06650560071689546);
+    p = fmaR(z, p, 0.07693274239195039);
+    p = fmaR(z, p, 0.09090872237804135);
+    p = fmaR(z, p, 0.11111111976861492);
+    p = fmaR(z, p, 0.14285714274058622);
+    p = fmaR(z, p, 0.20000000000077559);
+    p = fmaR(z, p, 0.33333333333333154);
+    return fmaR(z, p, 1.0);
+}
+// ln(1 + x) for x in [-1/2, 1], s = x / (2 + x): 19 FP64 instructions, within two ulp
+__device__ __forceinline__ double log1p_mid(double x) {
+    const double s = x * rcpR(2.0 + x);
+    return 2.0 * s * atanh_poly(s * s);
+}
+__device__ __forceinline__ float log1p_mid(float x) { return log1pR(x); }
+template <typename R> constexpr R log1p_mid_limit() { return sizeof(R) == 8 ? R(0.5) : R(0); }
 template <typename R> constexpr R log1p_small_limit() { return sizeof(R) == 8 ? R(1.0 / 64.0) : R(1.0 / 32.0); }
 
 template <typename R>
@@ -464,8 +491,14 @@ __device__ __forceinline__ R exact_gamma(const KbcNode<R>& n, const Coef<R>& K) 
 #pragma unroll
             for (int i = 0; i < 9; ++i) {
                 ok = ok && (x[i] > R(-1));
-                F = fmaR(dh[i], log1pR(x[i]), F);
                 D = fmaR(-K.beta * dh[i] * hw[i], rcpR(R(1) + x[i]), D);
+            }
+            if (amax <= log1p_mid_limit<R>()) {
+#pragma unroll
+                for (int i = 0; i < 9; ++i) F = fmaR(dh[i], log1p_mid(x[i]), F);
+            } else {
+#pragma unroll
+                for (int i = 0; i < 9; ++i) F = fmaR(dh[i], log1pR(x[i]), F);
             }
             if (!ok || !(D < R(0))) break;
             step = -divR(F, D);

@@ -22,8 +22,8 @@
 //     127, 1024^2 15.7 / 15.7; FP16 KBC-B 4096^2 97 / 93.
 //
 // Two steps stay where arithmetic binds: FP16 KBC inside the last-level cache
-// (1536^2 16.1 / 16.2) and the exact stabiliser beyond one tile per CU (1024^2
-// 15.0 / 16.7).
+// (1536^2 16.1 / 16.2), the exact stabiliser beyond one tile per CU (1024^2
+// 15.0 / 16.7) and in FP64 everywhere (FP64_EXACT).
 #include "kbc_launch.hpp"
 #include "kbc_tilen.hpp"
 
@@ -104,7 +104,8 @@ int step4_shape(const Lattice& L, const int32_t* sizes, int count, double state_
     // one tile per CU (an ensemble's launches are built for many).  Two rows only up to half of that: a tile's six margin
     // rows weigh most there (192^2 with 288 such tiles 1.82, with four rows
     // 1.44).  FP64 has room for fewer waves' registers, and not for 28 rows.
-    const bool f64 = L.form == F64;
+    const bool f64 = L.form == F64, exact = L.collision != LBGK && L.gamma_mode == GEXACT;
+    if (f64 && exact) return 0;
     if (one_per_cu) {
         if (tiles(2) <= kCus / 2) return shape(2, 10);
         if (tiles(4) <= kCus) return shape(4, 12);
@@ -118,7 +119,7 @@ int step4_shape(const Lattice& L, const int32_t* sizes, int count, double state_
     // many tiles per CU.  Plain stores matter to the light collisions only,
     // which the last-level cache feeds (FP32 LBGK 1280^2: plain 7.1, others
     // 8.6); KBC measures the same or 1 % better with non-temporal ones.
-    if (L.collision != LBGK && L.gamma_mode == GEXACT) return 0;
+    if (exact) return 0;
     const bool light = L.collision == LBGK || L.gamma_mode == GFIX;
     if (f64) return L.collision == LBGK ? shape(12, 12, nt != 0) : shape(12, 8, !light || nt != 0);
     if (L.form == F16) {
