@@ -76,7 +76,7 @@ typedef enum { LBM_KBC_A = 0, LBM_KBC_B = 1, LBM_KBC_C = 2, LBM_KBC_D = 3 } lbm_
 typedef enum { LBM_F16DEV_F32 = 0, LBM_F32DEV_F32 = 1, LBM_F64 = 2 } lbm_form;
 /* stabiliser: gamma* of eq. (result21) with the denominator guard, a fixed
  * value (gamma_fixed; 2 gives LBGK, 1/beta the regularised model), or the
- * root of eq. (result1) by Newton iteration from gamma* (guarded nodes keep
+ * root of eq. (result1) by iteration from gamma* (guarded nodes keep
  * gamma = 2; the iteration stops when a logarithm's argument would leave
  * (0, inf), after a step below 1e-15 (FP64) or 5e-7 (FP32 arithmetic)
  * relative, after a step that is not at most half the previous one (rounding
@@ -157,9 +157,9 @@ int lbm_init(lbm_ctx** out, const lbm_params* p, void* buf_a, void* buf_b, size_
              const double* rho, const double* ux, const double* uy, const double* grad,
              int32_t mode);
 
-/* Advance nsteps >= 0 time steps of eq. (Egeneral).  By default every pair of
- * steps is one launch (two fused pull-stream + collide steps, the first step's
- * result kept in LDS; see lbm_set_fusion) and an odd remainder one single-step
+/* Advance nsteps >= 0 time steps of eq. (Egeneral).  By default two or four
+ * steps are one launch (fused pull-stream + collide steps, the states between
+ * them kept in LDS; see lbm_set_fusion) and an odd remainder one single-step
  * launch; each launch reads one buffer and writes the other.  Enqueues only;
  * does no value checks (see lbm_diagnostics).  A slab (lbm_set_halo) takes
  * at most one launch's steps per call. */
@@ -440,7 +440,7 @@ int lbm_ensemble_set_fusion(lbm_ens* e, int32_t steps_per_launch, int32_t rows);
 int lbm_ensemble_get_fusion(const lbm_ens* e, int32_t* rows);
 
 /* Advance every member nsteps of eq. (Egeneral).
- *   persistent = 0: one launch per step, or per pair of steps with
+ *   persistent = 0: one launch per step, or per two or four steps with
  *     lbm_ensemble_set_fusion(2), over all members' tiles;
  *   persistent = 1: ONE launch for all the steps (pairs of fused steps, or
  *     single steps with fusion 1; an odd step left over by the pairs runs as

@@ -8,7 +8,7 @@ backward pass walks the segments from last to first, recomputes the K states
 of a segment from its checkpoint into K - 1 slots, and runs the hand-written
 adjoint step kernel back through them, then the adjoint of the initial state.
 By default (``overlap=True``) one native call runs all segments: each launch
-runs one adjoint step of the current segment and one recomputation step of
+runs two adjoint steps of the current segment and two recomputation steps of
 the next, which uses a second slot set.  Memory is about 2 sqrt(nsteps) states (3 with overlap); the
 recomputation adds one forward step per step.
 """

@@ -82,7 +82,7 @@ def _time(run, steps: int, reps: int) -> float:
 
 def _model_key(params) -> list[str]:
     # the stabiliser mode and guard change the per-node cost (the exact root
-    # runs a Newton iteration), so a choice made for one is not reused for another
+    # runs an iteration), so a choice made for one is not reused for another
     return [str(params.collision), str(params.variant), f"gm{params.gamma_mode}", f"guard{params.gamma_guard:.3e}"]
 
 

@@ -7,7 +7,7 @@
 // eq. (result21) is by default differentiated with the rest of the collision through
 // <ds|dh>, <dh|dh> and the entropic weights 1/feq; where the denominator guard
 // selects gamma = 2 it is a constant.  The exact stabiliser (the root of
-// eq. (result1), found by Newton's method) is differentiated by the implicit
+// eq. (result1), found by iteration) is differentiated by the implicit
 // function theorem at the root: for F(gamma; ds, dh, 1/feq, beta) = 0,
 // d gamma = -(dF at fixed gamma) / F'(gamma).  The forward quantities of the KBC
 // collision come from kbc_forward(), the code collide() runs, so both take the

@@ -247,7 +247,7 @@ struct AdjPairOp {
 
 }  // namespace
 
-// The exact stabiliser keeps single steps: its Newton iteration makes the ring
+// The exact stabiliser keeps single steps: its iteration makes the ring
 // dearer than what the second launch costs.
 bool adjoint_pairs(const Lattice& L) { return L.collision == LBGK || L.gamma_mode != GEXACT; }
 

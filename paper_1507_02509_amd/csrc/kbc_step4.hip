@@ -23,7 +23,8 @@
 //
 // Two steps stay where arithmetic binds: FP16 KBC inside the last-level cache
 // (1536^2 16.1 / 16.2), the exact stabiliser beyond one tile per CU (1024^2
-// 15.0 / 16.7) and in FP64 everywhere (FP64_EXACT).
+// 15.0 / 16.7) and in FP64 beyond the two-row tiles (64^2 22 / 13, 300 x 217
+// 18 / 23, 512^2 29 / 33).
 #include "kbc_launch.hpp"
 #include "kbc_tilen.hpp"
 
@@ -105,9 +106,9 @@ int step4_shape(const Lattice& L, const int32_t* sizes, int count, double state_
     // rows weigh most there (192^2 with 288 such tiles 1.82, with four rows
     // 1.44).  FP64 has room for fewer waves' registers, and not for 28 rows.
     const bool f64 = L.form == F64, exact = L.collision != LBGK && L.gamma_mode == GEXACT;
-    if (f64 && exact) return 0;
     if (one_per_cu) {
         if (tiles(2) <= kCus / 2) return shape(2, 10);
+        if (f64 && exact) return 0;
         if (tiles(4) <= kCus) return shape(4, 12);
         if (tiles(8) <= kCus) return shape(8, 16);
         if (tiles(12) <= kCus) return shape(12, f64 ? 12 : 16);

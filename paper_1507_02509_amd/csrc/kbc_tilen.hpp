@@ -232,14 +232,14 @@ int step4_many(int code, const Launch& l) {
     return -1;
 }
 
-// The shapes of at most one tile per CU, for every collision but FP64's exact
-// stabiliser.
+// The shapes of at most one tile per CU, for every collision (FP64's exact
+// stabiliser: the lowest only).
 template <int FORM, int COLL, int VAR, int GM, typename Launch>
 int step4_one(int code, const Launch& l) {
+    if (code == step4_code(2, 10)) return l.template at<2, 10, true>();
     if constexpr (FORM != F64 || COLL != KBCC || GM != GEXACT) {
         constexpr int w = FORM == F64 ? 12 : 16;
         switch (code) {
-            case step4_code(2, 10): return l.template at<2, 10, true>();
             case step4_code(4, 12): return l.template at<4, 12, true>();
             case step4_code(8, 16): return l.template at<8, 16, true>();
             case step4_code(12, w): return l.template at<12, w, true>();
