@@ -51,9 +51,8 @@ STEP_SOURCES = [os.path.join(_CSRC, f)
 # <ds|ds> branch (28): "compiled-instruction FLOPs", not a minimal operation
 # count of the method.  The vector peaks are MI355X's
 # published ones; the FP32 one assumes packed FP32 (two lanes per
-# instruction), which this library never issues, so at most half of it is
-# attainable here.
-FLOPS_PER_NODE_STEP = {"f32": 224, "f16": 260, "f64": 312}
+# instruction), which this library never issues.
+FLOPS_PER_NODE_STEP = {"f32": 224, "f16": 248, "f64": 312}
 VECTOR_PEAK_TFLOPS = {"f32": 157.3, "f16": 157.3, "f64": 78.6}
 VALU_ISSUE_PEAK = 256 * 64 * 2.4e9   # lane-instructions/s: 256 CUs, 64 lanes, nominal clock
 # untimed steps before each extra measurement, so that none is timed while the
@@ -440,8 +439,7 @@ def main():
                     "frac": round(achieved / peak, 4), "traffic": traffic, "kernel": kname,
                     "flops_kind": "FP32 operations of the compiled collision per node-step "
                                   f"({FLOPS_PER_NODE_STEP[args.form]}; FMA = 2), x {spl} steps x nodes per launch",
-                    "peak_kind": "published FP32 vector peak, which assumes packed FP32; this library issues "
-                                 "no packed FP32, so non-packed issue reaches at most half of it",
+                    "peak_kind": "published FP32 vector peak, which assumes packed FP32; this library issues none",
                     "steps_per_launch": spl, "algorithmic_flops_per_launch": flops_launch,
                     "algorithmic_bytes_per_launch": bytes_launch,
                     # the HBM side of the same launch: the state read and written once per launch
@@ -449,8 +447,8 @@ def main():
                     "hbm_frac_per_launch": round(hbm_gbs / HBM_PEAK_GBS, 4)}
         # the kernel's own limit: vector instructions issued (counted by the
         # profiler per node-step) against one instruction per lane and clock
-        # on 256 CUs x 64 lanes at the nominal 2.4 GHz (packed FP32 is not
-        # emitted, so the published FP32 peak above is twice what it can reach)
+        # on 256 CUs x 64 lanes at the nominal 2.4 GHz (plain FP32 ones of
+        # different waves can issue closer, reciprocals take four times as long)
         ipn = measured_traffic(key, field="valu_instructions_per_node_step")
         if ipn:
             roofline["valu_instructions_per_node_step"] = ipn
