@@ -13,9 +13,10 @@ namespace {
 
 // one workgroup per 64 x TH output tile
 template <int FORM, int COLL, int VAR, int GM, int TH, int NW, bool NT>
-__global__ __launch_bounds__(64 * NW) void k_ens4(const EnsEntry* __restrict__ tab,
-                                                  const int32_t* __restrict__ tile_member, int ntiles, int per_xcd,
-                                                  int parity) {
+__global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(stepn_waves<FORM, GM, NW>())))
+void k_ens4(const EnsEntry* __restrict__ tab,
+            const int32_t* __restrict__ tile_member, int ntiles, int per_xcd,
+            int parity) {
     using F = Form<FORM>;
     using S = typename F::S;
     using R = typename F::R;

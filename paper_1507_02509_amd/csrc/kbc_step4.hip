@@ -42,10 +42,11 @@ constexpr int tasks_of(int rows) {
 }
 
 template <int FORM, int COLL, int VAR, int GM, int TH, int NW, bool NT>
-__global__ __launch_bounds__(64 * NW) void k_step4(const typename Form<FORM>::S* __restrict__ src,
-                                                   typename Form<FORM>::S* __restrict__ dst, int nx, int ny,
-                                                   int64_t pitch, int ntx, int nty, int per_xcd,
-                                                   Coef<typename Form<FORM>::R> K) {
+__global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(stepn_waves<FORM, GM, NW>())))
+void k_step4(const typename Form<FORM>::S* __restrict__ src,
+             typename Form<FORM>::S* __restrict__ dst, int nx, int ny,
+             int64_t pitch, int ntx, int nty, int per_xcd,
+             Coef<typename Form<FORM>::R> K) {
     const int b = blockIdx.x;
     const int u = (b & 7) * per_xcd + (b >> 3);
     if (u >= ntx * nty) return;   // the whole workgroup leaves together

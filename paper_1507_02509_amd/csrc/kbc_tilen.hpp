@@ -193,6 +193,15 @@ __device__ __forceinline__ void stepn_tile(const typename Form<FORM>::S* __restr
     stepn_rest<FORM, COLL, VAR, GM, T, TH, NW, NT, 2>(win, dst, nx, ny, pitch, x0, y0, th, lane, w, K);
 }
 
+// Waves per SIMD a four-step kernel is compiled for: what one workgroup needs,
+// and for FP64's tile of eight waves what two workgroups per CU need: left
+// alone KBC-B takes 132 registers, which leaves one (1024^2 18.5 us per step, 14.1
+// with 128).
+template <int FORM, int GM, int NW>
+constexpr int stepn_waves() {
+    return FORM == F64 && NW == 8 && GM != GEXACT ? 4 : (NW + 3) / 4;
+}
+
 // Launch shapes of four steps: tile rows, waves per workgroup and store kind
 // as one code, and the call of a launcher's at<TH, NW, NT>() for a code.
 constexpr int step4_code(int rows, int waves, bool nt = true) { return rows | waves << 8 | (nt ? 1 << 16 : 0); }
