@@ -110,9 +110,9 @@ __device__ __forceinline__ void collide_vjp(const R (&g)[9], const R (&mu)[9], c
         ux = n.ux;
         uy = n.uy;
         const bool active = n.active;
-        R gam = n.gam;
+        R gam = n.gam, bg = K.beta * gam;
         if constexpr (GM == GEXACT) {
-            if (active) gam = exact_gamma<R>(n, K);
+            if (active) gam = exact_gamma<R>(n, K, bg);
         }
 
         // --------------------------------------------------------- reverse
@@ -120,7 +120,7 @@ __device__ __forceinline__ void collide_vjp(const R (&g)[9], const R (&mu)[9], c
         // adjoints of the scaled populations s_i node_scale(i), h_i node_scale(i)
         R m[9], sb[9], hb[9];
         R mdh = R(0), mds = R(0);
-        const R tb = R(2) * K.beta, bg = K.beta * gam;
+        const R tb = R(2) * K.beta;
 #pragma unroll
         for (int i = 0; i < 9; ++i) {
             lam[i] = mu[i];
@@ -148,7 +148,7 @@ __device__ __forceinline__ void collide_vjp(const R (&g)[9], const R (&mu)[9], c
                     // F'(gamma) = -beta sum_i dh_i^2 wr_i / (1 + x_i)
                     R ds[9], dh[9], w[9];
                     unscaled(n, ds, dh, w);
-                    const R om = R(1) - K.beta * gam, tbm1 = R(2) * K.beta - R(1);
+                    const R om = R(1) - bg, tbm1 = R(2) * K.beta - R(1);
                     R wr[9], y[9], r[9], lg[9];
                     R D = R(0);
                     bool ok = true;

@@ -384,15 +384,15 @@ __device__ __forceinline__ void kbc_forward(const R (&g)[9], const Coef<R>& K, K
 // the iteration.
 //
 // In that regime a step is not Newton's but third order (Schroeder's method:
-// the inverse series of F).  With t_i = (dh_i / feq_i) / (1 + x_i) and
-// A_k = sum_i dh_i t_i^k, all of which come with the evaluation of F,
+// the inverse series of F).  With q_i = (dh_i / feq_i) / (1 + x_i) and
+// A_k = sum_i dh_i q_i^k, all of which come with the evaluation of F,
 //   F(gamma + eta / beta) = F - A_1 eta - A_2 eta^2 / 2 - A_3 eta^3 / 3 - ...,
 // so with e = F / A_1, u = A_2 e / (2 A_1), v = A_3 e^2 / (3 A_1) the root is at
-//   eta = e (1 - u + 2 u^2 - v + O((e t)^3)).
-// e t is of the order of x^2, so one evaluation (about 160 instructions) mostly
+//   eta = e (1 - u + 2 u^2 - v + O((e q)^3)).
+// e q is of the order of x^2, so one evaluation (about 160 instructions) mostly
 // does what three of Newton's (125 each) did; the iteration also stops when
 // the third-order term itself is below the tolerance (what remains is smaller
-// by another factor e t).  FP32 KBC-B, 1024^2, 10 steps: 144 us, 265 with
+// by another factor e q).  FP32 KBC-B, 1024^2, 10 steps: 140 us, 265 with
 // Newton's.
 __device__ __forceinline__ float log1p_small(float x) {
     float p = fmaR(x, -1.0f / 6.0f, 0.2f);
@@ -416,10 +416,11 @@ __device__ __forceinline__ double log1p_small(double x) {
     p = fmaR(x, p, 1.0);
     return x * p;
 }
-// atanh(s) = s P(s^2) for s^2 = z <= 1/9, i.e. logarithms 2 atanh(s) of
-// arguments in [1/2, 2]: P the polynomial of degree 10 with the smallest
-// largest relative error (1.3e-18; coefficients by Remez's exchange algorithm).
-__device__ __forceinline__ double atanh_poly(double z) {
+// atanh(s) = s P(s^2), P(z) = 1 + z T(z), for s^2 = z <= 1/9, i.e. logarithms
+// 2 atanh(s) of arguments in [1/2, 2]: P the polynomial of degree 10 with the
+// smallest largest relative error (coefficients by Remez's exchange algorithm;
+// 2.5e-18 with the coefficients rounded as below).
+__device__ __forceinline__ double atanh_tail(double z) {
     double p = 0.08504923007075064;
     p = fmaR(z, p, 0.04172462195061191);
     p = fmaR(z, p, 0.06052477641340325);
@@ -429,24 +430,39 @@ __device__ __forceinline__ double atanh_poly(double z) {
     p = fmaR(z, p, 0.11111111976861492);
     p = fmaR(z, p, 0.14285714274058622);
     p = fmaR(z, p, 0.20000000000077559);
-    p = fmaR(z, p, 0.33333333333333154);
-    return fmaR(z, p, 1.0);
+    return fmaR(z, p, 0.33333333333333154);
 }
-// ln(1 + x) for x in [-1/2, 1], s = x / (2 + x): 19 FP64 instructions, within two ulp
-__device__ __forceinline__ double log1p_mid(double x) {
-    const double s = x * rcpR(2.0 + x);
-    return 2.0 * s * atanh_poly(s * s);
+__device__ __forceinline__ double atanh_poly(double z) { return fmaR(z, atanh_tail(z), 1.0); }
+// ln(1 + x) = 2 atanh(x / (2 + x)) for x in [-1/2, 1/2], given r = 1 / (2 + x) to
+// a few units in the last place: within 0.56 ulp (0.83 for the host's library
+// log1p).  The quotient is carried as s + sl, with tl the rounding error of
+// t = 2 + x and sl the remainder x - s (t + tl) over t; the leading part 2 s is
+// added last.  (With the quotient as the one product x r the error reaches 3.3
+// ulp, and the 99th percentile of the error in gamma grows by 11 %.)  What that takes is
+// mostly paid for by the one reciprocal that 1 / (1 + x) and 1 / (2 + x) share:
+// 1024^2 FP64 KBC-B 75 -> 78 us per step.
+__device__ __forceinline__ double log1p_mid(double x, double r) {
+    const double t = 2.0 + x, tl = x - (t - 2.0), s = x * r;
+    const double sl = fmaR(-s, tl, fmaR(-s, t, x)) * r;
+    const double z = s * s;
+    return fmaR(2.0, fmaR(s * z, atanh_tail(z), fmaR(z, sl, sl)), 2.0 * s);
 }
-__device__ __forceinline__ float log1p_mid(float x) { return log1pR(x); }
+__device__ __forceinline__ float log1p_mid(float x, float) { return log1pR(x); }
 template <typename R> constexpr R log1p_mid_limit() { return sizeof(R) == 8 ? R(0.5) : R(0); }
 template <typename R> constexpr R log1p_small_limit() { return sizeof(R) == 8 ? R(1.0 / 64.0) : R(1.0 / 32.0); }
 
+// The iteration for the root.  It runs on t = beta gamma, which is what the
+// collision multiplies dh by (returned in t): with gamma as the iterate the
+// rounding of beta gamma comes on top, and near equilibrium, where an evaluation
+// or two end the iteration, it raises the rms error of the populations (FP64
+// KBC-D) to 1.10 .. 1.14 times that with the root correctly rounded, 1.01 with t.
+// Returns gamma = t / beta.
 template <typename R>
-__device__ __forceinline__ R exact_gamma(const KbcNode<R>& n, const Coef<R>& K) {
+__device__ __forceinline__ R exact_gamma(const KbcNode<R>& n, const Coef<R>& K, R& t) {
     constexpr int kMaxIt = sizeof(R) == 8 ? 100 : 20;
     const R tol = sizeof(R) == 8 ? R(1e-15) : R(5e-7);
     const R tbm1 = R(2) * K.beta - R(1);
-    R gam = n.gam;
+    t = K.beta * n.gam;
     R dh[9], hw[9], sw[9];   // dh_i, dh_i / feq_i, (2 beta - 1) ds_i / feq_i
     const R irs[3] = {R(0.5) * n.ir, n.ir, R(2) * n.ir};
 #pragma unroll
@@ -458,7 +474,7 @@ __device__ __forceinline__ R exact_gamma(const KbcNode<R>& n, const Coef<R>& K) 
     }
     R prev = R(1e30);   // size of the previous step
     for (int it = 0; it < kMaxIt; ++it) {
-        const R om = R(1) - K.beta * gam;
+        const R om = R(1) - t;
         R x[9];
         R amax = R(0);
 #pragma unroll
@@ -466,17 +482,17 @@ __device__ __forceinline__ R exact_gamma(const KbcNode<R>& n, const Coef<R>& K) 
             x[i] = fmaR(om, hw[i], -sw[i]);
             amax = fmax(amax, fabs(x[i]));
         }
-        R step, rest;   // step in gamma; bound of what the step leaves, relative to it
+        R step, rest;   // step in t; bound of what the step leaves, relative to it
         if (amax < log1p_small_limit<R>()) {
             R F = R(0), A1 = R(0), A2 = R(0), A3 = R(0);
 #pragma unroll
             for (int i = 0; i < 9; ++i) {
                 F = fmaR(dh[i], log1p_small(x[i]), F);
-                const R t = hw[i] * rcpR(R(1) + x[i]);
-                const R m = dh[i] * t, mt = m * t;
+                const R q = hw[i] * rcpR(R(1) + x[i]);
+                const R m = dh[i] * q, mq = m * q;
                 A1 += m;
-                A2 += mt;
-                A3 = fmaR(mt, t, A3);
+                A2 += mq;
+                A3 = fmaR(mq, q, A3);
             }
             if (!(A1 > R(0))) break;
             const R ia = rcpR(A1);
@@ -484,33 +500,38 @@ __device__ __forceinline__ R exact_gamma(const KbcNode<R>& n, const Coef<R>& K) 
             const R u = R(0.5) * A2 * ia * e1, v = R(1.0 / 3.0) * A3 * ia * e1 * e1;
             const R uu = R(2) * u * u;
             const bool series = uu + v < R(1.0 / 64.0);
-            step = K.inv_beta * (series ? e1 * ((R(1) - u) + (uu - v)) : e1);
+            step = series ? e1 * ((R(1) - u) + (uu - v)) : e1;
             rest = series ? uu + v : R(1);
         } else {
             bool ok = true;
             R F = R(0), D = R(0);
-#pragma unroll
-            for (int i = 0; i < 9; ++i) {
-                ok = ok && (x[i] > R(-1));
-                D = fmaR(-K.beta * dh[i] * hw[i], rcpR(R(1) + x[i]), D);
-            }
             if (amax <= log1p_mid_limit<R>()) {
+                // one reciprocal for 1 / (1 + x) and 1 / (2 + x)
 #pragma unroll
-                for (int i = 0; i < 9; ++i) F = fmaR(dh[i], log1p_mid(x[i]), F);
+                for (int i = 0; i < 9; ++i) {
+                    const R a = R(1) + x[i], b = R(2) + x[i], r = rcpR(a * b);
+                    F = fmaR(dh[i], log1p_mid(x[i], a * r), F);
+                    D = fmaR(-dh[i] * hw[i], b * r, D);
+                }
             } else {
 #pragma unroll
-                for (int i = 0; i < 9; ++i) F = fmaR(dh[i], log1pR(x[i]), F);
+                for (int i = 0; i < 9; ++i) {
+                    ok = ok && (x[i] > R(-1));
+                    F = fmaR(dh[i], log1pR(x[i]), F);
+                    D = fmaR(-dh[i] * hw[i], rcpR(R(1) + x[i]), D);
+                }
             }
             if (!ok || !(D < R(0))) break;
             step = -divR(F, D);
             rest = R(1);
         }
-        gam += step;
+        t += step;
         const R as = fabs(step);
-        if (as * rest <= tol * fabs(gam) || as > R(0.5) * prev) break;
+        if (as * rest <= tol * fabs(t) || as > R(0.5) * prev) break;
         prev = as;
     }
-    return gam;
+    const R q = t * K.inv_beta;
+    return fmaR(fmaR(-q, K.beta, t), K.inv_beta, q);
 }
 
 // ds, dh and w of a node in their own units.
@@ -572,12 +593,17 @@ __device__ __forceinline__ R collide_units(R (&g)[9], const Coef<R>& K) {
         KbcNode<R> n;
         kbc_forward_sums<R, VAR, (GM == GEXACT ? GEST : GM), U, Q>(p, add_rest, K, n);
         R gam = n.gam;
+        R bgam = K.beta * gam;
         if constexpr (GM == GEXACT) {
-            if (n.active) gam = exact_gamma<R>(n, K);
+            if (n.active) gam = exact_gamma<R>(n, K, bgam);
         }
         // f' = f - beta (2 ds + gamma dh), eqs. (Egeneral), (ksh-mirror)
         const R tb[3] = {(R(4) * rz) * K.beta, R(2) * K.beta, R(Q) * K.beta};
-        const R bg[3] = {((R(2) * rz) * K.beta) * gam, K.beta * gam, ((R(0.5) * R(Q)) * K.beta) * gam};
+        R bg[3] = {((R(2) * rz) * K.beta) * gam, bgam, ((R(0.5) * R(Q)) * K.beta) * gam};
+        if constexpr (GM == GEXACT) {
+            bg[0] = (R(2) * rz) * bgam;
+            bg[2] = (R(0.5) * R(Q)) * bgam;
+        }
 #pragma unroll
         for (int i = 0; i < 9; ++i) {
             const int k = i == 0 ? 0 : (i < 5 ? 1 : 2);
