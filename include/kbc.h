@@ -235,6 +235,14 @@ int lbm_get_tile(const lbm_ctx* c, int32_t* width, int32_t* rows_per_thread, int
 int lbm_set_fusion(lbm_ctx* c, int32_t steps_per_launch, int32_t rows);
 int lbm_get_fusion(const lbm_ctx* c, int32_t* rows);
 
+/* How lbm_step(c, nsteps) would divide its steps with the current settings:
+ * split[0], split[1] and split[2] receive the steps that run in launches of
+ * four, of two and of one step.  tile (nullable) receives rows, waves per
+ * workgroup and flags (LBM_TILE_NONTEMPORAL or 0) of the tile of the launches
+ * of four, zeros where there is none.  Launches nothing.  LBM_EINVAL for a
+ * NULL ctx or split and for the nsteps that lbm_step refuses. */
+int lbm_get_split(const lbm_ctx* c, int32_t nsteps, int32_t* split, int32_t* tile);
+
 /* Slab mode: the context's lattice is one slab of a larger domain split in y
  * (one slab per GPU), periodic in x only.  The step's pull (eq. Egeneral:
  * population i arrives from x - v_i) then reads the two rows on each side of
@@ -438,6 +446,10 @@ int lbm_ensemble_set_tile(lbm_ens* e, int32_t width, int32_t rows_per_thread, in
  * synchronises the stream. */
 int lbm_ensemble_set_fusion(lbm_ens* e, int32_t steps_per_launch, int32_t rows);
 int lbm_ensemble_get_fusion(const lbm_ens* e, int32_t* rows);
+
+/* lbm_get_split for lbm_ensemble_step(e, nsteps, persistent) (the pairs and
+ * single steps of a persistent run share its launch). */
+int lbm_ensemble_get_split(const lbm_ens* e, int32_t nsteps, int32_t persistent, int32_t* split, int32_t* tile);
 
 /* Advance every member nsteps of eq. (Egeneral).
  *   persistent = 0: one launch per step, or per two or four steps with

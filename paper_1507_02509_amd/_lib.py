@@ -69,6 +69,7 @@ _SIGS = {
     "lbm_set_fusion": (_c.c_int, [_vp, _c.c_int32, _c.c_int32]),
     "lbm_spectra": (_c.c_int, [_vp, _c.c_int32, _vp, _vp]),
     "lbm_get_fusion": (_c.c_int, [_vp, _c.POINTER(_c.c_int32)]),
+    "lbm_get_split": (_c.c_int, [_vp, _c.c_int32, _c.POINTER(_c.c_int32), _c.POINTER(_c.c_int32)]),
     "lbm_set_graph": (_c.c_int, [_vp, _c.c_int32]),
     "lbm_set_halo": (_c.c_int, [_vp, _vp, _vp]),
     "lbm_get_edge_rows": (_c.c_int, [_vp, _vp, _vp]),
@@ -81,6 +82,8 @@ _SIGS = {
     "lbm_ensemble_step": (_c.c_int, [_vp, _c.c_int32, _c.c_int32]),
     "lbm_ensemble_set_fusion": (_c.c_int, [_vp, _c.c_int32, _c.c_int32]),
     "lbm_ensemble_get_fusion": (_c.c_int, [_vp, _c.POINTER(_c.c_int32)]),
+    "lbm_ensemble_get_split": (_c.c_int, [_vp, _c.c_int32, _c.c_int32, _c.POINTER(_c.c_int32),
+                                          _c.POINTER(_c.c_int32)]),
     "lbm_ensemble_blocks": (_c.c_int, [_vp]),
     "lbm_ensemble_set_spin_limit": (_c.c_int, [_vp, _c.c_uint32]),
     "lbm_ensemble_check": (_c.c_int, [_vp]),
@@ -132,6 +135,11 @@ def check(rc: int, what: str = ""):
         msg = load().lbm_last_error().decode(errors="replace")
         raise KbcError(rc, f"{what}: {msg}" if what else msg)
     return rc
+
+
+def split_dict(split, tile) -> dict:
+    """The arrays of lbm_get_split as a dict (see Sim.split)."""
+    return {4: split[0], 2: split[1], 1: split[2], "tile4": (tile[0], tile[1], bool(tile[2] & 1)) if tile[0] else None}
 
 
 def ptr(t) -> int | None:

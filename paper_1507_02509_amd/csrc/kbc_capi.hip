@@ -226,41 +226,66 @@ int lbm_init(lbm_ctx** out, const lbm_params* p, void* buf_a, void* buf_b, size_
 
 namespace {
 
+// How a call's steps are divided: launches of four fused steps, of two, and of one.
+struct StepSplit {
+    int32_t fours, pairs, singles;
+};
+
+// Four steps per launch in groups of eight where that pays (shape4, a
+// step4_shape code): each two such launches take the place of four launches of two
+// steps, so the state ends in the same buffer as without them (an ensemble's
+// members must agree on it).
+StepSplit split_steps(int32_t nsteps, int fuse, int shape4) {
+    StepSplit n{};
+    if (shape4) n.fours = nsteps / 8 * 2;
+    if (fuse == 2) n.pairs = (nsteps - 4 * n.fours) / 2;
+    n.singles = nsteps - 4 * n.fours - 2 * n.pairs;
+    return n;
+}
+
+// The shape of lbm_step's launches of four steps (0: none): not with a fused
+// tile of the caller's own.
+int four_shape(const lbm_ctx* c) {
+    if (c->fuse != 2 || c->fuse_rows != c->default_rows) return 0;
+    const int32_t size[2] = {c->p.nx, c->p.ny};
+    return kbc::step4_shape(c->L, size, 1, c->state_bytes, c->shape.nt, true);
+}
+
 // The launches of nsteps steps on c->L.stream, with the context's buffer
 // index and step counter advanced as they are enqueued.
 int step_eager(lbm_ctx* c, int32_t nsteps) {
-    int32_t s = 0;
-    // Four steps per launch where that pays, unless the caller has chosen
-    // another fused tile.  An even number of such launches: each takes the
-    // place of two launches of two steps, so the state ends in the same buffer
-    // as without them (an ensemble's members must agree on it).
-    const int32_t size[2] = {c->p.nx, c->p.ny};
-    const int shape4 = (c->fuse == 2 && c->fuse_rows == c->default_rows && nsteps >= 8)
-                           ? kbc::step4_shape(c->L, size, 1, c->state_bytes, c->shape.nt, true) : 0;
-    if (shape4) {
-        for (; s + 8 <= nsteps; s += 8)
-            for (int k = 0; k < 2; ++k) {
-                const int rc = kbc::launch_step4(c->L, c->buf[c->cur], c->buf[c->cur ^ 1], shape4);
-                if (rc) return launch_result(rc, "lbm_step (four fused steps)");
-                c->cur ^= 1;
-                c->steps += 4;
-            }
+    const int shape4 = nsteps >= 8 ? four_shape(c) : 0;
+    const StepSplit n = split_steps(nsteps, c->fuse, shape4);
+    for (int32_t k = 0; k < n.fours; ++k) {
+        const int rc = kbc::launch_step4(c->L, c->buf[c->cur], c->buf[c->cur ^ 1], shape4);
+        if (rc) return launch_result(rc, "lbm_step (four fused steps)");
+        c->cur ^= 1;
+        c->steps += 4;
     }
-    if (c->fuse == 2) {
-        for (; s + 2 <= nsteps; s += 2) {
-            const int rc = kbc::launch_step2(c->L, c->buf[c->cur], c->buf[c->cur ^ 1], c->fuse_rows, c->shape.nt);
-            if (rc) return launch_result(rc, "lbm_step (two fused steps)");
-            c->cur ^= 1;
-            c->steps += 2;
-        }
+    for (int32_t k = 0; k < n.pairs; ++k) {
+        const int rc = kbc::launch_step2(c->L, c->buf[c->cur], c->buf[c->cur ^ 1], c->fuse_rows, c->shape.nt);
+        if (rc) return launch_result(rc, "lbm_step (two fused steps)");
+        c->cur ^= 1;
+        c->steps += 2;
     }
-    for (; s < nsteps; ++s) {
+    for (int32_t k = 0; k < n.singles; ++k) {
         const int rc = kbc::launch_step(c->L, c->buf[c->cur], c->buf[c->cur ^ 1], c->shape);
         if (rc) return launch_result(rc, "lbm_step");
         c->cur ^= 1;
         ++c->steps;
     }
     return LBM_OK;
+}
+
+// What lbm_get_split and lbm_ensemble_get_split report.
+void put_split(const StepSplit& n, int shape4, int32_t* split, int32_t* tile) {
+    split[0] = 4 * n.fours;
+    split[1] = 2 * n.pairs;
+    split[2] = n.singles;
+    if (!tile) return;
+    tile[0] = n.fours ? kbc::step4_rows(shape4) : 0;
+    tile[1] = n.fours ? kbc::step4_waves(shape4) : 0;
+    tile[2] = n.fours && kbc::step4_nt(shape4) ? LBM_TILE_NONTEMPORAL : 0;
 }
 
 // Discard the captured graphs (after a change to what the launches do).
@@ -344,6 +369,26 @@ int lbm_step(lbm_ctx* c, int32_t nsteps) {
         }
     }
     return step_eager(c, nsteps);
+}
+
+int lbm_get_split(const lbm_ctx* c, int32_t nsteps, int32_t* split, int32_t* tile) {
+    if (!c || !split) return fail(LBM_EINVAL, "ctx and split must not be NULL");
+    if (nsteps < 0) return fail(LBM_EINVAL, "nsteps must be >= 0");
+    if (c->L.halo_lo && nsteps > c->fuse)
+        return fail(LBM_EINVAL, "a slab steps at most %d step(s) per call (its halo holds the rows for one launch)",
+                    c->fuse);
+    const int shape4 = four_shape(c);
+    int32_t rest = nsteps;
+    StepSplit n{};
+    if (c->graph_chunk >= 2) {
+        const int32_t replays = nsteps / c->graph_chunk;
+        const StepSplit g = split_steps(c->graph_chunk, c->fuse, shape4);
+        n = {replays * g.fours, replays * g.pairs, replays * g.singles};
+        rest -= replays * c->graph_chunk;
+    }
+    const StepSplit r = split_steps(rest, c->fuse, shape4);
+    put_split({n.fours + r.fours, n.pairs + r.pairs, n.singles + r.singles}, shape4, split, tile);
+    return LBM_OK;
 }
 
 int lbm_set_graph(lbm_ctx* c, int32_t chunk) {
@@ -977,6 +1022,11 @@ int ens_build(lbm_ens* e) {
     return LBM_OK;
 }
 
+StepSplit ens_split(const lbm_ens* e, int32_t nsteps, int32_t persistent) {
+    const bool four = e->fuse == 2 && e->rows == e->default_rows && !persistent;
+    return split_steps(nsteps, e->fuse, four ? e->shape4 : 0);
+}
+
 }  // namespace
 
 int lbm_set_halo(lbm_ctx* c, const void* lo, const void* hi) {
@@ -1142,11 +1192,8 @@ int lbm_ensemble_step(lbm_ens* e, int32_t nsteps, int32_t persistent) {
     const int cur = e->m[0]->cur;
     for (size_t r = 1; r < e->m.size(); ++r)
         if (e->m[r]->cur != cur) return fail(LBM_EINVAL, "members hold their states in different buffers");
-    // four steps per launch as in lbm_step: an even number of such launches,
-    // so that the members' states end in the same buffers as without them
-    const int fours = (e->fuse == 2 && e->rows == e->default_rows && e->shape4 && !persistent) ? nsteps / 8 * 2 : 0;
-    const int pairs = (e->fuse == 2) ? (nsteps - 4 * fours) / 2 : 0;
-    const int singles = nsteps - 4 * fours - 2 * pairs;
+    const StepSplit n = ens_split(e, nsteps, persistent);
+    const int fours = n.fours, pairs = n.pairs, singles = n.singles;
     kbc::EnsLaunch a{};
     a.nmem = static_cast<int>(e->m.size());
     a.sync = e->dsync;
@@ -1193,6 +1240,14 @@ int lbm_ensemble_step(lbm_ens* e, int32_t nsteps, int32_t persistent) {
         c->cur = par;
         c->steps += nsteps;
     }
+    return LBM_OK;
+}
+
+int lbm_ensemble_get_split(const lbm_ens* e, int32_t nsteps, int32_t persistent, int32_t* split, int32_t* tile) {
+    if (!e || !split) return fail(LBM_EINVAL, "ensemble and split must not be NULL");
+    if (nsteps < 0) return fail(LBM_EINVAL, "nsteps must be >= 0");
+    if (persistent != 0 && persistent != 1) return fail(LBM_EINVAL, "persistent must be 0 or 1");
+    put_split(ens_split(e, nsteps, persistent), e->shape4, split, tile);
     return LBM_OK;
 }
 

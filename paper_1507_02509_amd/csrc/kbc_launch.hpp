@@ -57,11 +57,12 @@ int launch_step2(const Lattice& L, const void* src, void* dst, int rows, int nt)
 // that beats two launches of two steps (0: none does) on `count` lattices of
 // sizes (nx, ny), (nx, ny), ... stepped together, whose buffers hold
 // state_bytes, with this store kind (one_per_cu: the launch has the shapes of
-// at most one tile per CU); rows and waves per workgroup of a code; and the
-// launch
+// at most one tile per CU); rows, waves per workgroup and store kind of a code;
+// and the launch
 int step4_shape(const Lattice& L, const int32_t* sizes, int count, double state_bytes, int nt, bool one_per_cu);
 inline int step4_rows(int code) { return code & 0xff; }
 inline int step4_waves(int code) { return code >> 8 & 0xff; }
+inline bool step4_nt(int code) { return (code >> 16 & 1) != 0; }
 int launch_step4(const Lattice& L, const void* src, void* dst, int shape);
 int launch_init(const Lattice& L, void* dst, const double* rho, const double* ux, const double* uy,
                 const double* grad, int mode);

@@ -57,6 +57,13 @@ class Ensemble:
     def fusion(self) -> int:
         return int(self.lib.lbm_ensemble_get_fusion(self.h, None))
 
+    def split(self, n: int, persistent: bool = False) -> dict:
+        """How step(n, persistent) would divide its steps (see Sim.split)."""
+        k, t = (ctypes.c_int32 * 3)(), (ctypes.c_int32 * 3)()
+        L.check(self.lib.lbm_ensemble_get_split(self.h, int(n), 1 if persistent else 0, k, t),
+                "lbm_ensemble_get_split")
+        return L.split_dict(k, t)
+
     def step(self, n: int = 1, persistent: bool = False) -> "Ensemble":
         """n steps of every member: one launch per step (or pair of fused
         steps), or with persistent=True one launch for all of them."""

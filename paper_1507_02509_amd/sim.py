@@ -126,6 +126,14 @@ class Sim:
         self.lib.lbm_get_fusion(self.ctx, ctypes.byref(r))
         return int(r.value)
 
+    def split(self, n: int) -> dict:
+        """How step(n) would divide its steps: {4: steps in launches of four,
+        2: of two, 1: of one, "tile4": (rows, waves per workgroup, nontemporal)
+        of the launches of four or None}."""
+        k, t = (ctypes.c_int32 * 3)(), (ctypes.c_int32 * 3)()
+        L.check(self.lib.lbm_get_split(self.ctx, int(n), k, t), "lbm_get_split")
+        return L.split_dict(k, t)
+
     # ------------------------------------------------------- slab of a domain
     def halo_buffers(self) -> tuple[torch.Tensor, torch.Tensor]:
         """Two zeroed [2, 9, pitch] buffers of the storage dtype: the shape of
