@@ -16,8 +16,9 @@ K timed steps.  `roofline` describes the dominant kernel: with several fused
 steps per launch it is bound by vector-ALU issue, so `bound` is "alu" and
 `achieved` counts the FP32 operations of its compiled collision against the
 published FP32 vector peak; the same object gives the HBM side per launch
-(72 B per node per launch over the launch time, against 8 TB/s).  With
---fusion 2,8 every launch runs two steps on 8-row tiles; with --fusion 1 (one
+(72 B per node per launch over the launch time, against 8 TB/s) and the launches
+that ran: K steps are launches of four in groups of eight and pairs for the
+rest.  With --fusion 2,8 every launch runs two steps on 8-row tiles; with --fusion 1 (one
 step per launch) the kernel is HBM-bound and `bound` is "hbm".
 `cpu_baseline` times the FP64 CPU oracle on a bounded sample of the same
 workload on all host cores (up to 16) and on one core.
@@ -106,19 +107,70 @@ def time_steps(sim, steps: int, warmup: int):
     return t0.elapsed_time(t1) / steps, wall
 
 
-def steps_per_launch(sim, n, form, collision="kbc", exact=False, chosen=False):
-    """Fused steps per launch of a long lbm_step on an n x n lattice.  With the
-    default fused tile that is four where the lattice has at most one tall tile
-    per CU, and elsewhere unless arithmetic binds two already (the exact
-    stabiliser; FP16 KBC inside the 256 MiB last-level cache); an explicitly
-    chosen launch (chosen) is taken to differ from the default."""
-    if sim.fusion != 2 or chosen:
-        return sim.fusion
-    tall = 16 if form == "f64" else 28
-    if -(-n // 64) * -(-n // tall) <= 256:
-        return 4
-    cached = BYTES_PER_NODE[form] * n * n <= 256 * 2 ** 20
-    return 2 if collision == "kbc" and (exact or (form == "f16" and cached)) else 4
+def load_kernels(form, variant, nu, seed, k0, dev):
+    """Eleven steps of a small lattice: two launches of four steps, one of two,
+    a single step.  The first launch of each kernel loads its code object, 9 ms
+    for the four-step kernels, which a warm-up of fewer than eight steps would
+    leave to the timed region."""
+    import torch
+    make_sim(128, form, "kbc", variant, nu, seed, k0, dev).step(11)
+    torch.cuda.synchronize()
+
+
+def mean_steps(split: dict) -> float:
+    """Steps per launch of a call, from Sim.split or Ensemble.split: the mean
+    over its launches (an int where all are alike)."""
+    launches = {k: split[k] // k for k in (4, 2, 1) if split[k]}
+    m = sum(k * v for k, v in launches.items()) / sum(launches.values())
+    return next(iter(launches)) if len(launches) == 1 else round(m, 4)
+
+
+def roofline(form, variant, n, split, rows, ms):
+    """The roofline object of a timed call of ms milliseconds per step on an
+    n x n lattice, divided as `split` says (Sim.split): per-launch figures are
+    means over the launches that ran, `kernel` names the one that ran most of
+    the steps."""
+    nodes = n * n
+    launches = {k: split[k] // k for k in (4, 2, 1) if split[k]}
+    total, steps = sum(launches.values()), sum(split[k] for k in launches)
+    spl = mean_steps(split)
+    names = {1: f"k_step<{form},KBC-{variant}>", 2: f"k_step2<{form},KBC-{variant},64x{rows}>",
+             4: f"k_step4<{form},KBC-{variant}>"}
+    kname = names[max(launches, key=lambda k: split[k])]
+    launch_ms = ms * steps / total
+    bytes_launch = BYTES_PER_NODE[form] * nodes      # state read + written once per launch
+    hbm_gbs = bytes_launch / (launch_ms * 1e-3) / 1e9
+    keys = {k: f"{form}_kbc{variant}_{n}" + (f"_fused{k}" if k > 1 else "") for k in launches}
+    measured = {k: measured_traffic(keys[k]) for k in launches}
+    traffic = None if None in measured.values() else round(sum(v * measured[k] for k, v in launches.items()) / total)
+    ran = {"steps_per_launch": spl, "launches": {names[k]: v for k, v in launches.items()}}
+    if set(launches) == {1} or variant != "B":
+        return {"bound": "hbm", "achieved": round(hbm_gbs, 1), "peak": HBM_PEAK_GBS, "unit": "GB/s",
+                "frac": round(hbm_gbs / HBM_PEAK_GBS, 4), "traffic": traffic, "kernel": kname, **ran,
+                "algorithmic_bytes_per_launch": bytes_launch}
+    # several steps per pass through HBM: the kernel is bound by vector
+    # arithmetic, not by HBM
+    flops_launch = round(FLOPS_PER_NODE_STEP[form] * nodes * steps / total)
+    achieved = flops_launch / (launch_ms * 1e-3) / 1e12
+    peak = VECTOR_PEAK_TFLOPS[form]
+    r = {"bound": "alu", "achieved": round(achieved, 2), "peak": peak, "unit": "TFLOP/s",
+         "frac": round(achieved / peak, 4), "traffic": traffic, "kernel": kname,
+         "flops_kind": "FP32 operations of the compiled collision per node-step "
+                       f"({FLOPS_PER_NODE_STEP[form]}; FMA = 2), x {spl} steps x nodes per launch",
+         "peak_kind": "published FP32 vector peak, which assumes packed FP32; this library issues none",
+         **ran, "algorithmic_flops_per_launch": flops_launch, "algorithmic_bytes_per_launch": bytes_launch,
+         # the HBM side of the same launches: the state read and written once per launch
+         "hbm_GBs_per_launch": round(hbm_gbs, 1), "hbm_frac_per_launch": round(hbm_gbs / HBM_PEAK_GBS, 4)}
+    # the kernels' own limit: vector instructions issued (counted by the
+    # profiler per node-step) against one instruction per lane and clock
+    # on 256 CUs x 64 lanes at the nominal 2.4 GHz (plain FP32 ones of
+    # different waves can issue closer, reciprocals take four times as long)
+    valu = {k: measured_traffic(keys[k], field="valu_instructions_per_node_step") for k in launches}
+    if None not in valu.values():
+        ipn = sum(split[k] * v for k, v in valu.items()) / steps
+        r["valu_instructions_per_node_step"] = round(ipn, 1)
+        r["valu_issue_frac"] = round(ipn * nodes / (ms * 1e-3) / VALU_ISSUE_PEAK, 4)
+    return r
 
 
 def make_sim(n, form, collision, variant, nu, seed, k0, device):
@@ -280,11 +332,11 @@ def time_ensemble(dev, steps=60, persistent_steps=2000):
     e1.record()
     torch.cuda.synchronize()
     ms = e0.elapsed_time(e1) / steps
-    spl = 4 if ens.fusion == 2 else ens.fusion      # 91 M nodes: beyond the last-level cache
+    spl = mean_steps(ens.split(steps))
     res = {"members": 256, "nodes": nodes, "ms_per_step": round(ms, 4),
            "mlups": round(nodes / (ms * 1e-3) / 1e6, 1), "steps_per_launch": spl,
            "hbm_frac": round(72 * nodes / (spl * ms * 1e-3) / 1e9 / HBM_PEAK_GBS, 4),
-           "launch": "one batched launch over all members per " + ("four steps" if spl == 4 else "step")}
+           "launch": f"one batched launch over all members per {spl} steps"}
     best, _ = autotune.tune_ensemble(ens, steps=10, reps=2, persistent=True, use_cache=False)
     blocks = ens.blocks
     ens.step(2, persistent=True)
@@ -407,12 +459,11 @@ def main():
 
     progress(f"init {n}x{n} {args.form} KBC-{args.variant}")
     sim = make_sim(n, args.form, "kbc", args.variant, nu, seed, k0, dev)
-    # an explicit fusion with the default rows is the default launch
-    rows0 = sim.fusion_rows
+    load_kernels(args.form, args.variant, nu, seed, k0, dev)
     if args.fusion is not None:
         sim.set_fusion(*args.fusion)
     rows = sim.fusion_rows
-    spl = steps_per_launch(sim, n, args.form, chosen=rows != rows0)
+    split = sim.split(args.steps)
     d0 = sim.diagnostics()
     ms, wall = time_steps(sim, args.steps, args.warmup)
     progress(f"timed {args.steps} steps: {ms:.4f} ms/step")
@@ -421,43 +472,6 @@ def main():
     torch.cuda.empty_cache()
     nodes = n * n
     mlups = nodes / (ms * 1e-3) / 1e6
-    launch_ms = ms * spl      # one launch advances spl steps (the default 200 steps are whole launches)
-    bytes_launch = BYTES_PER_NODE[args.form] * nodes      # state read + written once per launch
-    hbm_gbs = bytes_launch / (launch_ms * 1e-3) / 1e9
-    key = f"{args.form}_kbc{args.variant}_{n}" + (f"_fused{spl}" if spl > 1 else "")
-    traffic = measured_traffic(key)
-    kname = {1: f"k_step<{args.form},KBC-{args.variant}>",
-             2: f"k_step2<{args.form},KBC-{args.variant},64x{rows}>",
-             4: f"k_step4<{args.form},KBC-{args.variant}>"}[spl]
-    if spl > 1 and args.variant == "B":
-        # several steps per pass through HBM: the kernel is bound by vector
-        # arithmetic, not by HBM
-        flops_launch = FLOPS_PER_NODE_STEP[args.form] * nodes * spl
-        achieved = flops_launch / (launch_ms * 1e-3) / 1e12
-        peak = VECTOR_PEAK_TFLOPS[args.form]
-        roofline = {"bound": "alu", "achieved": round(achieved, 2), "peak": peak, "unit": "TFLOP/s",
-                    "frac": round(achieved / peak, 4), "traffic": traffic, "kernel": kname,
-                    "flops_kind": "FP32 operations of the compiled collision per node-step "
-                                  f"({FLOPS_PER_NODE_STEP[args.form]}; FMA = 2), x {spl} steps x nodes per launch",
-                    "peak_kind": "published FP32 vector peak, which assumes packed FP32; this library issues none",
-                    "steps_per_launch": spl, "algorithmic_flops_per_launch": flops_launch,
-                    "algorithmic_bytes_per_launch": bytes_launch,
-                    # the HBM side of the same launch: the state read and written once per launch
-                    "hbm_GBs_per_launch": round(hbm_gbs, 1),
-                    "hbm_frac_per_launch": round(hbm_gbs / HBM_PEAK_GBS, 4)}
-        # the kernel's own limit: vector instructions issued (counted by the
-        # profiler per node-step) against one instruction per lane and clock
-        # on 256 CUs x 64 lanes at the nominal 2.4 GHz (plain FP32 ones of
-        # different waves can issue closer, reciprocals take four times as long)
-        ipn = measured_traffic(key, field="valu_instructions_per_node_step")
-        if ipn:
-            roofline["valu_instructions_per_node_step"] = ipn
-            roofline["valu_issue_frac"] = round(ipn * nodes / (ms * 1e-3) / VALU_ISSUE_PEAK, 4)
-    else:
-        roofline = {"bound": "hbm", "achieved": round(hbm_gbs, 1), "peak": HBM_PEAK_GBS, "unit": "GB/s",
-                    "frac": round(hbm_gbs / HBM_PEAK_GBS, 4), "traffic": traffic, "kernel": kname,
-                    "steps_per_launch": spl, "algorithmic_bytes_per_launch": bytes_launch}
-
     extras = {}
     want = set() if args.no_extras else set(args.extras.split(","))
     if want:
@@ -466,7 +480,7 @@ def main():
             if form == args.form or "forms" not in want:
                 continue
             s = make_sim(n, form, "kbc", args.variant, nu, seed, k0, dev)
-            fs = steps_per_launch(s, n, form)
+            fs = mean_steps(s.split(args.extra_steps))
             m, _ = time_steps(s, args.extra_steps, EXTRA_WARMUP)
             progress(f"{form}: {m:.4f} ms/step")
             del s
@@ -483,7 +497,7 @@ def main():
         s = Sim(n, n, beta_from_nu(nu), collision="kbc", variant=args.variant, form=args.form,
                 gamma_mode="exact", device=dev).init(ux, uy)
         del ux, uy
-        fs = steps_per_launch(s, n, args.form, exact=True)
+        fs = mean_steps(s.split(args.extra_steps))
         m, _ = time_steps(s, args.extra_steps, EXTRA_WARMUP)
         progress(f"exact stabiliser: {m:.4f} ms/step")
         d = s.diagnostics()
@@ -494,7 +508,7 @@ def main():
             "over_estimate_time": round(m / ms, 3), "gamma_mean": d["gamma"]}
     if "lbgk" in want:
         s = make_sim(n, args.form, "lbgk", "A", nu, seed, k0, dev)
-        fs = steps_per_launch(s, n, args.form, collision="lbgk")
+        fs = mean_steps(s.split(args.extra_steps))
         m, _ = time_steps(s, args.extra_steps, EXTRA_WARMUP)
         del s
         torch.cuda.empty_cache()
@@ -572,7 +586,7 @@ def main():
         "config": {"workload": workload, "nx": n, "ny": n, "collision": f"KBC-{args.variant}",
                    "form": f"{args.form}dev" if args.form != "f64" else "f64", "nu": nu, "seed": seed,
                    "k0": k0, "u_rms": 0.05, "init": "grad_cd"},
-        "roofline": roofline,
+        "roofline": roofline(args.form, args.variant, n, split, rows, ms),
         "wall_s_timed": round(wall, 3),
         "final_state": {"steps": args.warmup + args.steps,
                         "mass_drift_rel": (d_main["mass"] - d0["mass"]) / d0["mass"],
