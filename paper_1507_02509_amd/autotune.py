@@ -2,15 +2,16 @@
 
 For a single lattice it times every candidate launch configuration -- the
 single-step kernel with each tile (width, rows per thread, non-temporal
-stores) and the two-step fused kernel with each tile height and store kind --
-on the caller's own lattice with HIP events; for an ensemble, every tile of
-the ensemble kernel.  It keeps the one with the smallest median time and
+stores) and the fused kernels with each tile height and store kind (the
+library's default height includes its launches of four steps, the others run
+two per launch) -- on the caller's own lattice with HIP events; for an ensemble,
+every tile of the ensemble kernel.  Every trial is a multiple of eight steps, so
+that launches of four are timed without pairs beside them.  It keeps the one with the smallest median time and
 caches the choice in a JSON file keyed by the device name and the
 configuration (form, collision, variant, stabiliser mode and guard, lattice
 sizes).
-The lattice state is restored afterwards: every trial takes an even number of
-steps and the state buffers are copied back, so tuning changes nothing but
-the tile.  Results of the step kernels are bitwise identical for every tile,
+The lattice state is restored afterwards (copied back), so tuning changes
+nothing but the tile.  Results of the step kernels are bitwise identical for every tile,
 so the choice only affects speed.
 """
 from __future__ import annotations
@@ -29,7 +30,8 @@ ENSEMBLE_TILES = [(w, r, nt) for (w, r) in ((128, 2), (256, 1), (256, 2)) for nt
 ENSEMBLE_CANDIDATES = ([("single",) + t for t in ENSEMBLE_TILES] +
                        [("fused", rows, nt) for rows in (8, 16) for nt in (False, True)])
 # launch configurations of a single lattice: ("single", width, rows per
-# thread, nt) or ("fused", tile rows, nt) (two steps per launch)
+# thread, nt) or ("fused", tile rows, nt) (two steps per launch, or four where
+# the library takes them with that tile)
 STEP_CANDIDATES = ([("single",) + t for t in STEP_TILES] +
                    [("fused", rows, nt) for rows in (8, 16, 24, 32) for nt in (False, True)])
 
@@ -80,6 +82,14 @@ def _time(run, steps: int, reps: int) -> float:
     return times[len(times) // 2]
 
 
+def _whole_groups(steps: int) -> int:
+    """Steps of a trial: whole groups of eight, the library's launches of four."""
+    return max(8, -(-steps // 8) * 8)
+
+
+# The first entry of a key names what the candidates launch: a new one for
+# every change of what a candidate means, so that a choice cached for the
+# kernels before it is not reused.
 def _model_key(params) -> list[str]:
     # the stabiliser mode and guard change the per-node cost (the exact root
     # runs an iteration), so a choice made for one is not reused for another
@@ -87,7 +97,7 @@ def _model_key(params) -> list[str]:
 
 
 def _sim_key(sim) -> str:
-    return "|".join(["sim3", torch.cuda.get_device_name(sim.device), str(sim.form), *_model_key(sim.params),
+    return "|".join(["sim4", torch.cuda.get_device_name(sim.device), str(sim.form), *_model_key(sim.params),
                      f"{sim.nx}x{sim.ny}"])
 
 
@@ -102,7 +112,7 @@ def tune_sim(sim, steps: int = 10, reps: int = 3, candidates=None, use_cache: bo
         best = tuple(cache[key]["tile"])
         apply_config(sim, best)
         return best, cache[key].get("ms", {})
-    steps += steps % 2
+    steps = _whole_groups(steps)
     snap = sim.state_buffer().clone()
     n0 = sim.steps
     timings = {}
@@ -110,7 +120,7 @@ def tune_sim(sim, steps: int = 10, reps: int = 3, candidates=None, use_cache: bo
         if cand[0] == "fused" and cand[1] == 32 and sim.form == _lib.F64:
             continue
         apply_config(sim, cand)
-        sim.step(2)
+        sim.step(8)
         timings[cand] = _time(sim.step, steps, reps)
     best = min(timings, key=timings.get)
     apply_config(sim, best)
@@ -137,7 +147,7 @@ def apply_ensemble_config(ens, cand):
 def _ens_key(ens) -> str:
     m0 = ens.members[0]
     sizes = hashlib.sha1(",".join(f"{m.nx}x{m.ny}" for m in ens.members).encode()).hexdigest()[:12]
-    return "|".join(["ensemble3", torch.cuda.get_device_name(m0.device), str(m0.form), *_model_key(m0.params),
+    return "|".join(["ensemble4", torch.cuda.get_device_name(m0.device), str(m0.form), *_model_key(m0.params),
                      str(len(ens.members)), sizes])
 
 
@@ -152,13 +162,13 @@ def tune_ensemble(ens, steps: int = 10, reps: int = 3, persistent: bool = False,
         best = tuple(cache[key]["tile"])
         apply_ensemble_config(ens, best)
         return best, cache[key].get("ms", {})
-    steps += steps % 2
+    steps = _whole_groups(steps)
     snaps = [m.state_buffer().clone() for m in ens.members]
     n0 = [m.steps for m in ens.members]
     timings = {}
     for cand in candidates or ENSEMBLE_CANDIDATES:
         apply_ensemble_config(ens, cand)
-        ens.step(2, persistent)
+        ens.step(8, persistent)
         timings[cand] = _time(lambda k: ens.step(k, persistent), steps, reps)
     best = min(timings, key=timings.get)
     apply_ensemble_config(ens, best)
