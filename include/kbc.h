@@ -228,8 +228,11 @@ int lbm_get_tile(const lbm_ctx* c, int32_t* width, int32_t* rows_per_thread, int
  * too.  LBM_EINVAL for other values.  With 2 and the default height, calls of
  * eight steps or more may run groups of eight as two launches of four fused
  * steps where that is faster (small lattices, and where two steps per launch
- * are bound by memory); the state ends in the same buffer as without, and KBC
- * writes it with non-temporal stores whatever the flag.  lbm_get_fusion
+ * are bound by memory); the state ends in the same buffer as without.  KBC's
+ * launches of four, and every collision's on small lattices, have non-temporal
+ * stores only: they take the place of pairs with the library's default store
+ * kind and with that flag, not where the caller has set plain stores against
+ * the default.  lbm_get_fusion
  * returns 1 or 2 as set and stores the fused tile height in *rows when rows is not NULL
  * (-1 for a NULL ctx). */
 int lbm_set_fusion(lbm_ctx* c, int32_t steps_per_launch, int32_t rows);
@@ -439,7 +442,7 @@ int lbm_ensemble_set_tile(lbm_ens* e, int32_t width, int32_t rows_per_thread, in
  * lbm_set_fusion for every member, 64 x `rows` tiles, rows in {8, 16}; 0
  * keeps the current height).  Defaults: 2 steps with 16 rows for FP32 and
  * FP16, 8 rows for FP64 (and, as in lbm_step, groups of eight steps as two
- * launches of four where that is faster).  Bitwise identical either way; the
+ * launches of four where that is faster and the store kind allows it).  Bitwise identical either way; the
  * non-temporal flag of lbm_ensemble_set_tile applies to both.
  * lbm_ensemble_get_fusion returns the steps per launch and stores the rows in
  * *rows when not NULL (-1 for a NULL ensemble).  set_fusion with new rows

@@ -27,6 +27,7 @@ struct lbm_ctx {
     int fuse;               // time steps per launch of lbm_step: 1 or 2
     int fuse_rows;          // output tile height of the fused launch: 8, 16, 24 or 32
     int default_rows;       // its default for this lattice
+    int default_nt;         // default store kind for this lattice
     double state_bytes;     // of both population buffers
     double* dscratch;       // diagnostics: block partials (device)
     double* dresult;        // diagnostics: sums (pinned host memory the kernel writes)
@@ -187,6 +188,7 @@ int lbm_init(lbm_ctx** out, const lbm_params* p, void* buf_a, void* buf_b, size_
     c->shape = default_shape(p->form);
     c->state_bytes = 2.0 * static_cast<double>(bytes);
     if (plain_stores_pay(p->form, c->state_bytes)) c->shape.nt = 0;
+    c->default_nt = c->shape.nt;
     // two fused steps per launch by default for every form (measured for
     // KBC-B at 16384^2: FP32 +38 %, FP64 +25 %, FP16 +6 % over single steps;
     // the ring of extra step-1 collisions costs less than the HBM pass it saves)
@@ -243,12 +245,18 @@ StepSplit split_steps(int32_t nsteps, int fuse, int shape4) {
     return n;
 }
 
+// Whether launches of four steps of this shape may stand in for pairs with the
+// store kind nt: most of their kernels have one kind only, the faster one, which
+// is no reason to overrule a caller who set the other.
+bool store_kind_ok(int shape4, int nt, int default_nt) { return nt == default_nt || (kbc::step4_nt(shape4) ? 1 : 0) == nt; }
+
 // The shape of lbm_step's launches of four steps (0: none): not with a fused
-// tile of the caller's own.
+// tile height, or a store kind that they do not have, of the caller's own.
 int four_shape(const lbm_ctx* c) {
     if (c->fuse != 2 || c->fuse_rows != c->default_rows) return 0;
     const int32_t size[2] = {c->p.nx, c->p.ny};
-    return kbc::step4_shape(c->L, size, 1, c->state_bytes, c->shape.nt, true);
+    const int shape4 = kbc::step4_shape(c->L, size, 1, c->state_bytes, c->shape.nt, true);
+    return store_kind_ok(shape4, c->shape.nt, c->default_nt) ? shape4 : 0;
 }
 
 // The launches of nsteps steps on c->L.stream, with the context's buffer
@@ -895,7 +903,8 @@ struct lbm_ens {
     int64_t dmap2_len;
     int32_t* dmap;              // member of each single-step tile
     int64_t dmap_len;
-    int default_rows;           // fused tile height the library chose
+    int default_rows;           // fused tile height and store kind the library chose
+    int default_nt;
     double state_bytes;         // of all members' buffers
     int shape4;                 // launch shape of four fused steps (0: pairs are as fast)
     kbc::EnsEntry* dtab4;       // member table, tile count and tile index for it
@@ -999,6 +1008,7 @@ int ens_build(lbm_ens* e) {
     }
     e->shape4 = kbc::step4_shape(e->L, sizes.data(), static_cast<int>(e->m.size()), e->state_bytes, e->shape.nt,
                                  false);
+    if (!store_kind_ok(e->shape4, e->shape.nt, e->default_nt)) e->shape4 = 0;
     if (e->shape4) {
         const int64_t tiles4 = ens_table(e, 64, kbc::step4_rows(e->shape4), tab);
         if (tiles4 < 0 || !kbc::grid_fits(8 * ((tiles4 + 7) / 8), 64 * kbc::step4_waves(e->shape4))) {
@@ -1088,6 +1098,7 @@ int lbm_ensemble_create(lbm_ens** out, lbm_ctx* const* members, int32_t count) {
             state += 2.0 * 9.0 * c->p.ny * static_cast<double>(c->L.pitch) * form_bytes(c->p.form);
         if (plain_stores_pay(m0->p.form, state)) e->shape.nt = 0;
         e->state_bytes = state;
+        e->default_nt = e->shape.nt;
     }
     e->shape4 = 0;
     e->dtab4 = nullptr;

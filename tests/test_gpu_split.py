@@ -116,3 +116,30 @@ def test_settings():
         with pytest.raises(L.KbcError) as e:
             s.split(n)
         assert e.value.code == L.LBM_EINVAL
+
+
+def test_store_kind_of_the_caller():
+    """A store kind set against the default is kept: pairs where the four-step
+    kernels do not have it, their other kind where they do."""
+    print("split store kind", flush=True)
+    s = make(130, 70)                                       # default: non-temporal
+    assert s.tile[2] and s.split(16)[4] == 16
+    s.set_tile(256, 1, False)
+    assert s.split(16) == {4: 0, 2: 16, 1: 0, "tile4": None}
+    s.set_tile(256, 1, True)
+    assert s.split(16)[4] == 16
+    s = make(1020, 1023)                                    # default: plain; the kernels write non-temporally
+    assert not s.tile[2] and s.split(16)["tile4"] == (16, 8, True)
+    s.set_tile(256, 1, True)
+    assert s.split(16)["tile4"] == (16, 8, True)
+    s = make(900, 701, collision="lbgk")                    # both kinds
+    assert s.split(16)["tile4"] == (12, 8, False)
+    s.set_tile(256, 1, True)
+    assert s.split(16)["tile4"][2] and s.split(16)[4] == 16
+    e = Ensemble([make(nx, ny) for nx, ny in BEYOND])
+    assert e.split(16)["tile4"] == (28, 12, True)
+    e.set_tile(256, 1, False)
+    assert e.split(16) == {4: 0, 2: 16, 1: 0, "tile4": None}
+    e.set_tile(256, 1, True)
+    assert e.split(16)[4] == 16
+    e.free()
