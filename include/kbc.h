@@ -411,6 +411,14 @@ int lbm_adjoint_rollout(lbm_ctx* c, const void* const* ckpts, int32_t nsteps, in
                         void* const* slots_a, void* const* slots_b, void* lam_in, void* lam_out, double* dbeta,
                         int32_t* which);
 
+/* Takes now the scratch that lbm_adjoint_rollout over nsteps steps in segments
+ * of seglen and lbm_adjoint_init after it need (at least four doubles a node,
+ * kept until lbm_free).  Optional: each of the two takes what it needs itself,
+ * but lbm_adjoint_init then grows the scratch, which synchronises the stream
+ * (0.2 ms in the middle of a backward pass).  LBM_ENOMEM leaves no scratch
+ * behind, and both calls as they are without it. */
+int lbm_adjoint_reserve(lbm_ctx* c, int32_t nsteps, int32_t seglen);
+
 /* Adjoint of lbm_init for modes LBM_INIT_EQ and LBM_INIT_GRAD_CD: from
  * lam0 = dL/df^0 and the initial fields (rho nullable = rho0), writes
  * dL/du_x, dL/du_y (dense FP64 [ny][nx]) and adds dL/dbeta of the initial

@@ -75,6 +75,7 @@ class _Rollout(torch.autograd.Function):
         if ctx.cfg.overlap and len(ctx.ckpts) > 1:
             slots_b = [sim.new_state() for _ in range(nslot)]
             ckpts = [ctx.ckpts[s] for s in sorted(ctx.ckpts.keys())]
+            sim.adjoint_reserve(N, K)     # adjoint_init follows below
             if sim.adjoint_rollout(ckpts, N, K, slots, slots_b, lam_a, lam_b, acc):
                 lam_a, lam_b = lam_b, lam_a
         else:

@@ -630,6 +630,24 @@ size_t init_scratch(const lbm_ctx* c) {
     const size_t N = static_cast<size_t>(c->p.nx) * c->p.ny;
     return init_offset(c) + (N + 255) / 256 + 4 * N;
 }
+
+// lbm_adjoint_rollout's scratch: a pair of steps' partials, one slice of sums per
+// step, their totals.  The steps' dL/dbeta slices are summed once at the end where
+// all of them take at most 64 MiB (two launches a pass instead of two a segment),
+// else segment by segment; the order of the additions is the same.
+struct RolloutScratch {
+    int64_t nb, ng, kr;   // partials, length of a slice, slices
+    bool once;
+    size_t elems() const { return static_cast<size_t>(nb + ng * kr + kr); }
+};
+RolloutScratch rollout_scratch(const lbm_ctx* c, int32_t nsteps, int32_t seglen, bool may_once) {
+    RolloutScratch r;
+    r.nb = kbc::adjoint_piece_partials(c->L);
+    r.ng = kbc::adjoint_piece_slice(c->L);
+    r.once = may_once && r.ng * nsteps <= (int64_t{8} << 20);
+    r.kr = (static_cast<int64_t>(r.once ? nsteps : seglen) + 63) / 64 * 64;
+    return r;
+}
 }  // namespace
 
 int lbm_set_adjoint_gamma(lbm_ctx* c, int32_t mode) {
@@ -777,6 +795,14 @@ int lbm_adjoint_segment(lbm_ctx* c, const void* state0, void* const* slots, int3
     return LBM_OK;
 }
 
+int lbm_adjoint_reserve(lbm_ctx* c, int32_t nsteps, int32_t seglen) {
+    if (!c) return fail(LBM_EINVAL, "ctx is NULL");
+    if (nsteps < 0 || seglen < 1) return fail(LBM_EINVAL, "nsteps must be >= 0 and seglen >= 1");
+    const int rc = ensure_ascratch(c, std::max(rollout_scratch(c, nsteps, seglen, true).elems(), init_scratch(c)));
+    if (rc == LBM_ENOMEM) (void)hipGetLastError();   // not for the next launch's check to find
+    return rc;
+}
+
 int lbm_adjoint_rollout(lbm_ctx* c, const void* const* ckpts, int32_t nsteps, int32_t seglen,
                         void* const* slots_a, void* const* slots_b, void* lam_in, void* lam_out, double* dbeta,
                         int32_t* which) {
@@ -791,27 +817,20 @@ int lbm_adjoint_rollout(lbm_ctx* c, const void* const* ckpts, int32_t nsteps, in
             if (!slots_a[i] || !slots_b[i] || slots_a[i] == slots_b[i])
                 return fail(LBM_EINVAL, "slot %d is NULL or shared by both sets", i);
     }
-    const int64_t nb = kbc::adjoint_piece_partials(c->L), ng = kbc::adjoint_piece_slice(c->L);
     const int pieces = kbc::adjoint_pieces(c->L);
     const bool pairs = kbc::adjoint_pairs(c->L);
-    // The steps' dL/dbeta slices are summed once at the end where all of them
-    // take at most 64 MiB (two launches a pass instead of two a segment), else
-    // segment by segment; the order of the additions is the same.
-    bool once = ng * nsteps <= (int64_t{8} << 20);
-    int64_t kr = (static_cast<int64_t>(once ? nsteps : seglen) + 63) / 64 * 64;
-    // room for lbm_adjoint_init too, which usually follows: growing the scratch
-    // then would synchronise (0.2 ms in the middle of a backward pass).  On a
-    // full device the segments' own room is enough.
-    int rc = ensure_ascratch(c, std::max(static_cast<size_t>(nb + ng * kr + kr), init_scratch(c)));
-    if (rc == LBM_ENOMEM) {
+    RolloutScratch room = rollout_scratch(c, nsteps, seglen, true);
+    int rc = ensure_ascratch(c, room.elems());
+    if (rc == LBM_ENOMEM && room.once) {   // on a full device the segments' own room is enough
         (void)hipGetLastError();
-        once = false;
-        kr = (static_cast<int64_t>(seglen) + 63) / 64 * 64;
-        rc = ensure_ascratch(c, static_cast<size_t>(nb + ng * kr + kr));
+        room = rollout_scratch(c, nsteps, seglen, false);
+        rc = ensure_ascratch(c, room.elems());
     }
     if (rc) return rc;
-    double* const slices = c->ascratch + nb;
-    double* const totals = slices + ng * kr;
+    const int64_t ng = room.ng;
+    const bool once = room.once;
+    double* const slices = c->ascratch + room.nb;
+    double* const totals = slices + ng * room.kr;
     void* const* sets[2] = {slots_a, slots_b};
     auto seg_len = [&](int32_t j) { return std::min(seglen, nsteps - j * seglen); };
     // source of recomputed state t + 1 (t = 0 .. k - 2) of segment j

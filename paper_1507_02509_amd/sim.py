@@ -304,6 +304,15 @@ class Sim:
                                              ctypes.byref(which)), "lbm_adjoint_rollout")
         return int(which.value)
 
+    def adjoint_reserve(self, nsteps: int, seglen: int) -> bool:
+        """Take the scratch of adjoint_rollout and of the adjoint_init after it
+        in one piece (lbm_adjoint_reserve); False, and nothing taken, where the
+        device has no room for that."""
+        rc = self.lib.lbm_adjoint_reserve(self.ctx, int(nsteps), int(seglen))
+        if rc != L.LBM_ENOMEM:
+            L.check(rc, "lbm_adjoint_reserve")
+        return rc == L.LBM_OK
+
     def adjoint_init(self, ux0, uy0, lam0, grad_ux, grad_uy, dbeta=None, rho=None, mode: str = "grad_cd"):
         L.check(self.lib.lbm_adjoint_init(self.ctx, L.ptr(rho), L.ptr(ux0), L.ptr(uy0), _INIT[mode], L.ptr(lam0),
                                           L.ptr(grad_ux), L.ptr(grad_uy), L.ptr(dbeta)), "lbm_adjoint_init")
