@@ -77,10 +77,12 @@ typedef enum { LBM_F16DEV_F32 = 0, LBM_F32DEV_F32 = 1, LBM_F64 = 2 } lbm_form;
 /* stabiliser: gamma* of eq. (result21) with the denominator guard, a fixed
  * value (gamma_fixed; 2 gives LBGK, 1/beta the regularised model), or the
  * root of eq. (result1) by iteration from gamma* (guarded nodes keep
- * gamma = 2; the iteration stops when a logarithm's argument would leave
- * (0, inf), after a step below 1e-15 (FP64) or 5e-7 (FP32 arithmetic)
- * relative, after a step that is not at most half the previous one (rounding
- * noise reached), or after 100 / 20 steps).  LBM_GAMMA_EXACT runs in the step,
+ * gamma = 2; the iteration, in beta gamma, stops when a logarithm's argument
+ * would leave (0, inf), after a step below 1e-15 (FP64) or 5e-7 (FP32
+ * arithmetic) relative, near equilibrium (every argument within 1/64 / 1/32 of
+ * 1, where its steps are third order) also once the third-order term of the step
+ * is below that, after a step that is not at most half the previous one
+ * (rounding noise reached), or after 100 / 20 steps).  LBM_GAMMA_EXACT runs in the step,
  * moments, diagnostics, the ensemble and the adjoint (which differentiates the
  * root by the implicit function theorem, holding gamma where the iteration
  * stopped without a root). */
@@ -127,10 +129,12 @@ typedef struct {
  * launch (earlier launches of the same call may have been enqueued).
  * Work-items per node: 1 / rows-per-thread for the single step (1/4 with the
  * FP16 default 256 x 4 tile, 1 with the FP32 and FP64 defaults), 4 / rows for
- * two fused steps (1/4 with 16-row tiles, 1/2 with FP64's 8), 1/4 to 1 for four
- * (whose launch is not chosen where it would not fit), 1 / (rows per
+ * two fused steps (1/4 with 16-row tiles, 1/2 with FP64's 8), waves / rows of
+ * the tile for four (0.3 to 1, and up to 5 on lattices of at most 256 tiles; not
+ * chosen where the launch would not fit), 1 / (rows per
  * thread) for the adjoint step (1/2 for FP32 and FP16 lattices of at least
- * 8192 tiles of 128 x 4 nodes, else 1), 1/4 or 1/2 for two adjoint steps, as
+ * 8192 tiles of 128 x 4 nodes, else 1), 4 / rows for two adjoint steps (1/4 or
+ * 1/2, and 1 on lattices of at most 256 four-row tiles), as
  * much again for the forward steps that lbm_adjoint_rollout combines with
  * them, and 1 for lbm_adjoint_init.  So every
  * lattice whose buffers fit the device's memory steps in the default

@@ -6,13 +6,13 @@ stores) and the fused kernels with each tile height and store kind (the
 library's default height includes its launches of four steps, the others run
 two per launch) -- on the caller's own lattice with HIP events; for an ensemble,
 every tile of the ensemble kernel.  Every trial is a multiple of eight steps, so
-that launches of four are timed without pairs beside them.  It keeps the one with the smallest median time and
-caches the choice in a JSON file keyed by the device name and the
-configuration (form, collision, variant, stabiliser mode and guard, lattice
-sizes).
+that launches of four are timed without pairs beside them.  It keeps the one
+with the smallest median time and caches the choice in a JSON file keyed by the
+device name and the configuration (form, collision, variant, stabiliser mode and
+guard, lattice sizes).
 The lattice state is restored afterwards (copied back), so tuning changes
-nothing but the tile.  Results of the step kernels are bitwise identical for every tile,
-so the choice only affects speed.
+nothing but the tile.  Results of the step kernels are bitwise identical for
+every tile, so the choice only affects speed.
 """
 from __future__ import annotations
 

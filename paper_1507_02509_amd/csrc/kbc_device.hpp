@@ -85,7 +85,7 @@ __device__ __forceinline__ float fmaR(float a, float b, float c) { return __buil
 __device__ __forceinline__ double fmaR(double a, double b, double c) { return __builtin_fma(a, b, c); }
 // reciprocal: v_rcp_f32 (1 ulp) in FP32; in FP64 v_rcp_f64 (good to 2^-24)
 // refined by one third-order step r <- r + r (e + e^2), e = 1 - a r, which
-// leaves e^3 = 2^-73: three FMAs where two Newton steps take four, and one
+// leaves e^3 = 2^-72: three FMAs where two Newton steps take four, and one
 // fewer in a row (without the scaling and final correction of the compiler's
 // own division: within about an ulp for the positive normal denominators used
 // here).  Of 2^22 arguments in [1/64, 8) both leave the same 1026 not correctly
@@ -372,11 +372,11 @@ __device__ __forceinline__ void kbc_forward(const R (&g)[9], const Coef<R>& K, K
 // equilibrium, ln(1 + x) is its Taylor polynomial, of degree 6 or 10, by
 // Horner's rule: six or ten FMAs against the general form's logarithm,
 // reciprocal and guard (FP32) or the library log1p (FP64).  The truncation is
-// below 1.4e-10 and 8e-20 relative, the evaluation within 1.2e-7 and an ulp.
+// below 1.4e-10 and 8e-20 relative, the evaluation within 1.2e-7 and 1.5 ulp.
 // Above that and up to 1/2 the FP64 logarithm is log1p_mid; the library's (about
 // 100 instructions, nine times an iteration) is left to nodes beyond.  A few
-// such nodes set the time of their waves: 300 x 217 FP64 KBC-B 51 -> 18 us per
-// step, 1024^2 225 -> 90, the adjoint step of 1024^2 353 -> 133.  The
+// such nodes set the time of their waves: 300 x 217 FP64 KBC-B 62 -> 8 us per
+// step, 1024^2 269 -> 77 (with the third-order steps below).  The
 // choice is the node's own (all nine of its arguments small), so a node's
 // result does not depend on which nodes share its wave; a wave skips the
 // general form when none of its nodes needs it.  The quantities that do not change
@@ -403,7 +403,7 @@ __device__ __forceinline__ float log1p_small(float x) {
     return x * p;
 }
 // FP64: below 1/64 the Taylor polynomial of degree 10 (truncation below
-// 8e-20 relative, evaluation within an ulp) replaces the library log1p
+// 8e-20 relative, evaluation within 1.5 ulp) replaces the library log1p
 __device__ __forceinline__ double log1p_small(double x) {
     double p = fmaR(x, -1.0 / 10.0, 1.0 / 9.0);
     p = fmaR(x, p, -1.0 / 8.0);

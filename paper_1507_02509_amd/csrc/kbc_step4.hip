@@ -2,29 +2,31 @@
 // tile body is stepn_tile (kbc_tilen.hpp).
 //
 // Where four steps pay against two (step4_shape), us per step with two / four
-// steps per launch:
+// steps per launch (of calls that are whole groups of eight; a call's other steps
+// run as pairs):
 //
 //   * Small lattices, at most one tile per CU.  There a launch is a chain of
 //     latencies (about 2.4 us for the launch itself, then the loads, then one
 //     collision after another), and the arithmetic repeated in the tiles'
 //     margins costs nothing while CUs are idle.  The smallest tile height that
 //     still gives every CU at most one tile is taken, with enough waves that
-//     each has one row or two per step.  FP32 KBC-B 64^2 2.55 / 1.27, 256^2 2.74 /
-//     1.51, 320^2 2.86 / 1.85, 384^2 3.48 / 2.23, 512^2 3.64 / 2.67, 640^2 4.60 /
-//     4.12; FP64 64^2 3.14 / 1.70, 512^2 5.31 / 4.44; FP16 512^2 3.80 / 3.03;
-//     FP32 LBGK 512^2 2.86 / 1.86; exact stabiliser FP32 512^2 9.03 / 6.94.
+//     each has one row or two per step.  FP32 KBC-B 64^2 2.59 / 1.32, 256^2 2.73 /
+//     1.52, 320^2 2.82 / 1.85, 384^2 3.46 / 2.15, 512^2 3.58 / 2.61, 640^2 4.52 /
+//     3.78; FP64 64^2 3.13 / 1.69, 512^2 5.00 / 4.19; FP16 512^2 3.61 / 2.61;
+//     FP32 LBGK 512^2 2.77 / 1.70; exact stabiliser FP32 128^2 12.0 / 5.4.
 //   * Larger ones that memory binds at two steps: LBGK and the fixed
 //     stabiliser in every form, FP32 and FP64 KBC, FP16 KBC beyond the
 //     last-level cache.  Four steps halve the traffic for a quarter more
-//     collisions in the margins.  FP32 LBGK 4096^2 117 / 68, FP64 LBGK 2048^2
-//     58.2 / 37.3, FP16 LBGK 3072^2 44.6 / 38.0; FP32 KBC-B 8192^2 477 / 391,
-//     4096^2 122 / 98, 1280^2 13.8 / 12.4, 1024^2 9.1 / 9.1; FP64 KBC-B 3072^2 138 /
-//     127, 1024^2 15.7 / 15.7; FP16 KBC-B 4096^2 97 / 93.
+//     collisions in the margins.  FP32 LBGK 4096^2 117 / 62, FP64 LBGK 2048^2
+//     55.4 / 34.3, FP16 LBGK 3072^2 41.9 / 28.9; FP32 KBC-B 8192^2 450 / 364,
+//     4096^2 115 / 92, 1280^2 12.0 / 11.3, 1024^2 8.2 / 7.7; FP64 KBC-B 3072^2 134 /
+//     110, 1024^2 14.9 / 13.4; FP16 KBC-B 4096^2 91 / 86.
 //
 // Two steps stay where arithmetic binds: FP16 KBC inside the last-level cache
 // (1536^2 16.1 / 16.2), the exact stabiliser beyond one tile per CU (1024^2
-// 15.0 / 16.7) and in FP64 beyond the two-row tiles (64^2 22 / 13, 300 x 217
-// 18 / 23, 512^2 29 / 33).
+// 15.0 / 16.7) and in FP64 beyond the two-row tiles (64^2 19 / 13, 300 x 217
+// 18 / 23, 512^2 29 / 33).  FP64's exact two-row kernel is held to the 168
+// registers of its ten waves and spills 65 (KBC-D) to 165 (KBC-A) more.
 #include "kbc_launch.hpp"
 #include "kbc_tilen.hpp"
 

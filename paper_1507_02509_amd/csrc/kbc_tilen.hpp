@@ -196,7 +196,7 @@ __device__ __forceinline__ void stepn_tile(const typename Form<FORM>::S* __restr
 // Waves per SIMD a four-step kernel is compiled for: what one workgroup needs,
 // and for FP64's tile of eight waves what two workgroups per CU need: left
 // alone KBC-B takes 132 registers, which leaves one (1024^2 18.5 us per step, 14.1
-// with 128).
+// with 128; KBC-A spills two registers for it).
 template <int FORM, int GM, int NW>
 constexpr int stepn_waves() {
     return FORM == F64 && NW == 8 && GM != GEXACT ? 4 : (NW + 3) / 4;

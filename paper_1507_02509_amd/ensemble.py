@@ -65,8 +65,8 @@ class Ensemble:
         return L.split_dict(k, t)
 
     def step(self, n: int = 1, persistent: bool = False) -> "Ensemble":
-        """n steps of every member: one launch per step (or pair of fused
-        steps), or with persistent=True one launch for all of them."""
+        """n steps of every member: one launch per step (or two or four fused
+        steps, see split), or with persistent=True one launch for all of them."""
         L.check(self.lib.lbm_ensemble_step(self.h, int(n), 1 if persistent else 0), "lbm_ensemble_step")
         return self
 

@@ -108,8 +108,9 @@ class Sim:
         return int(self.lib.lbm_get_graph(self.ctx))
 
     def set_fusion(self, steps_per_launch: int, rows: int = 0):
-        """Time steps per kernel launch (1, or 2 = two fused steps) and the
-        fused tile height (8, 16, 24 or 32 rows; 0 keeps the current one)."""
+        """Time steps per kernel launch (1, or 2 = two fused steps, or four where
+        that is faster with the default height: see split) and the fused tile
+        height (8, 16, 24 or 32 rows; 0 keeps the current one)."""
         self._fusion = (int(steps_per_launch), int(rows))
         if self.ctx:
             L.check(self.lib.lbm_set_fusion(self.ctx, *self._fusion), "lbm_set_fusion")
@@ -293,9 +294,10 @@ class Sim:
     def adjoint_rollout(self, ckpts, nsteps: int, seglen: int, slots_a, slots_b, lam_in, lam_out,
                         dbeta=None) -> int:
         """The whole backward pass over checkpoints ckpts (f^0, f^seglen, ...),
-        each launch running one adjoint step and one recomputation step of the
-        next segment (see lbm_adjoint_rollout); returns 0 if dL/df^0 is in
-        lam_in, 1 if in lam_out."""
+        each launch running two adjoint steps (one for the exact stabiliser) and
+        as many recomputation steps of the next segment (see
+        lbm_adjoint_rollout); returns 0 if dL/df^0 is in lam_in, 1 if in
+        lam_out."""
         def arr(ts):
             return (ctypes.c_void_p * max(1, len(ts)))(*[L.ptr(t) for t in ts]) if ts else None
         which = ctypes.c_int32(-1)
